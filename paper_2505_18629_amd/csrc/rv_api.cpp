@@ -290,22 +290,34 @@ struct Prof {
   }
 };
 
-// The matmul launch shape for this model's element type and epilogue
-// (plan_matmul in rv_plan.h).
-GemmPlan plan_gemm(int dtype, int epi, int M, int N, int K, bool allow_split, int part_rows) {
-  return plan_matmul(dtype == RV_BF16, epi == EPI_SWIGLU, M, N, K, allow_split, part_rows);
+constexpr double kQkvSplitUs = 4.0;  // a split QKV projection's finish kernel, beside its traffic
+
+// Launch shape of one matmul of this model: plan_wide's, else plan_matmul's.
+struct MatPlan {
+  WidePlan wide;
+  GemmPlan gemm;
+  int gk() const { return wide.use ? wide.gk : gemm.gk; }
+};
+
+MatPlan plan_mat(const rv_cache* c, int epi, int M, int N, int K, bool allow_split, double split_us = 0) {
+  const bool bf16 = c->m->cfg.dtype == RV_BF16;
+  MatPlan p{};
+  if (bf16) p.wide = plan_wide(M, N, K, allow_split, c->gpart_rows, split_us);
+  if (!p.wide.use) p.gemm = plan_matmul(bf16, epi == EPI_SWIGLU, M, N, K, allow_split, c->gpart_rows);
+  return p;
 }
 
-hipError_t run_gemm(const rv_cache* c, int epi, GemmArgs g, bool allow_split, hipStream_t st,
-                    int* gk_out = nullptr) {
-  const int dtype = c->m->cfg.dtype;
-  const GemmPlan p = plan_gemm(dtype, epi, g.M, g.N, g.K, allow_split, c->gpart_rows);
-  g.n_tg = p.n_tg;
-  g.gk = p.gk;
-  if (gk_out) *gk_out = p.gk;
-  const int e = (epi == EPI_RESID && p.gk > 1) ? EPI_PARTIAL : epi;
-  if (p.tiled) return launch_gemm_tiled(e, g, p.nw, p.nt, p.mtt, st);
-  return launch_gemm(dtype, e, g, p.nt, p.mtt, st);
+// EPI_RESID of a split plan writes its k-group partials (EPI_PARTIAL).
+hipError_t run_gemm(const rv_cache* c, int epi, GemmArgs g, const MatPlan& p, hipStream_t st) {
+  g.gk = p.gk();
+  if (epi == EPI_RESID && g.gk > 1) epi = EPI_PARTIAL;
+  if (p.wide.use) {
+    g.n_tg = p.wide.n_tg;
+    return launch_gemm_wide(epi, g, p.wide.rows256, p.wide.mt, st);
+  }
+  g.n_tg = p.gemm.n_tg;
+  if (p.gemm.tiled) return launch_gemm_tiled(epi, g, st);
+  return launch_gemm(c->m->cfg.dtype, epi, g, p.gemm.nt, p.gemm.mtt, st);
 }
 
 // Runs every decoder layer over the current row plan (h filled, segments set).
@@ -348,6 +360,15 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
   at.out = c->att;
   at.out2 = c->att2;
   at.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
+
+  // the same launch shapes in every layer
+  const int qd = mc.n_heads * hd;
+  const MatPlan p_qkv = plan_mat(c, EPI_RESID, M, m->qkv.N, d, true, kQkvSplitUs);
+  const MatPlan p_qkv1 = p_qkv.gk() > 1 ? p_qkv : plan_mat(c, EPI_QKV, M, m->qkv.N, d, false);
+  const MatPlan p_o = plan_mat(c, EPI_RESID, M, d, qd, true);
+  const MatPlan p_gateup = plan_mat(c, EPI_SWIGLU, M, m->gateup.N, d, false);
+  const MatPlan p_down = plan_mat(c, EPI_RESID, M, d, mc.ffn_dim, true);
+  const MatPlan p_last = split_last ? p_down : plan_mat(c, EPI_RESID, M, d, mc.ffn_dim, false);
 
   int pending = 0;  // k-groups of the last residual matmul still in c->gpart
   for (int l = 0; l < mc.n_layers; ++l) {
@@ -393,17 +414,15 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
       // agent-scope release per workgroup, an L2 writeback each: measured
       // slower than the extra launch.)
       Prof pf(c, RV_PROF_QKV, st);
-      const GemmPlan qp = plan_gemm(dt, EPI_RESID, M, g.N, g.K, true, c->gpart_rows);
-      if (qp.gk > 1) {
+      if (p_qkv.gk() > 1) {
         g.P = c->gpart;
         g.ldy = g.N;
-        int gk = 1;
-        HIP_TRY(run_gemm(c, EPI_RESID, g, true, st, &gk), "qkv");
-        QkvFinish qf{c->gpart, gk, M, g.N, g.q_rows, g.k_rows, hd, mc.n_heads, mc.n_kv_heads, c->kv_len,
+        HIP_TRY(run_gemm(c, EPI_RESID, g, p_qkv, st), "qkv");
+        QkvFinish qf{c->gpart, p_qkv.gk(), M, g.N, g.q_rows, g.k_rows, hd, mc.n_heads, mc.n_kv_heads, c->kv_len,
                      c->row_pos, c->row_seq, c->rope_cos, c->rope_sin, c->qbuf, c->qbuf2, kc, vc, kc2, vc2};
         HIP_TRY(launch_qkv_finish(dt, qf, st), "qkv finish");
       } else {
-        HIP_TRY(run_gemm(c, EPI_QKV, g, false, st), "qkv");
+        HIP_TRY(run_gemm(c, EPI_QKV, g, p_qkv1, st), "qkv");
       }
     }
 
@@ -426,13 +445,14 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
     go.X2 = c->att2;
     go.M = M;
     go.N = d;
-    go.K = mc.n_heads * hd;
+    go.K = qd;
     go.Y = c->h;
     go.ldy = d;
     go.P = c->gpart;
     {
       Prof pf(c, RV_PROF_O, st);
-      HIP_TRY(run_gemm(c, EPI_RESID, go, true, st, &pending), "o-proj");
+      HIP_TRY(run_gemm(c, EPI_RESID, go, p_o, st), "o-proj");
+      pending = p_o.gk();
     }
 
     {
@@ -453,7 +473,7 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
     gu.ld_act = mc.ffn_dim;
     {
       Prof pf(c, RV_PROF_GATEUP, st);
-      HIP_TRY(run_gemm(c, EPI_SWIGLU, gu, false, st), "gate/up");
+      HIP_TRY(run_gemm(c, EPI_SWIGLU, gu, p_gateup, st), "gate/up");
     }
 
     GemmArgs gd{};
@@ -468,7 +488,9 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
     gd.P = c->gpart;
     {
       Prof pf(c, RV_PROF_DOWN, st);
-      HIP_TRY(run_gemm(c, EPI_RESID, gd, split_last || l + 1 < mc.n_layers, st, &pending), "down");
+      const MatPlan& pd = l + 1 < mc.n_layers ? p_down : p_last;
+      HIP_TRY(run_gemm(c, EPI_RESID, gd, pd, st), "down");
+      pending = pd.gk();
     }
   }
   if (pending_out) *pending_out = pending;
@@ -854,7 +876,7 @@ rv_status verify_impl(rv_cache* c, const int32_t* h_prefix_len, const int32_t* d
   gl.ldy = mc.vocab;
   {
     Prof pf(c, RV_PROF_LMHEAD, st);
-    HIP_TRY(run_gemm(c, EPI_STORE, gl, false, st), "lm head");
+    HIP_TRY(run_gemm(c, EPI_STORE, gl, plan_mat(c, EPI_STORE, gl.M, gl.N, gl.K, false), st), "lm head");
   }
 
   HeadArgs ha = head_args(c, k, kb, R1, n_probe, P, *fusion, d_q, seed, d_draft_ids, h_prefix_len, d_accept_len,
@@ -1130,19 +1152,19 @@ rv_status rv_debug_time_matrix(rv_cache* c, int32_t matrix, int32_t M, int32_t r
       case RV_MAT_O:
         g.W = m->w_o[l]; g.X = c->att; g.X2 = c->att2; g.N = d; g.K = mc.n_heads * mc.head_dim;
         g.Y = c->h; g.ldy = d; g.P = c->gpart;
-        return run_gemm(c, EPI_RESID, g, true, st);
+        return run_gemm(c, EPI_RESID, g, plan_mat(c, EPI_RESID, g.M, g.N, g.K, true), st);
       case RV_MAT_GATEUP:
         g.W = m->w_gateup[l]; g.X = c->xn; g.X2 = c->xn2; g.N = m->gateup.N; g.K = d;
         g.act = c->act; g.act2 = c->act2;
-        return run_gemm(c, EPI_SWIGLU, g, false, st);
+        return run_gemm(c, EPI_SWIGLU, g, plan_mat(c, EPI_SWIGLU, g.M, g.N, g.K, false), st);
       case RV_MAT_DOWN:
         g.W = m->w_down[l]; g.X = c->act; g.X2 = c->act2; g.N = d; g.K = mc.ffn_dim;
         g.Y = c->h; g.ldy = d; g.P = c->gpart;
-        return run_gemm(c, EPI_RESID, g, true, st);
+        return run_gemm(c, EPI_RESID, g, plan_mat(c, EPI_RESID, g.M, g.N, g.K, true), st);
       default:
         g.W = m->lm_head; g.X = c->lm_x; g.X2 = c->lm_x2; g.N = mc.vocab; g.K = d;
         g.Y = c->logits; g.ldy = mc.vocab;
-        return run_gemm(c, EPI_STORE, g, false, st);
+        return run_gemm(c, EPI_STORE, g, plan_mat(c, EPI_STORE, g.M, g.N, g.K, false), st);
     }
   };
   if (matrix == RV_MAT_LM_HEAD && M > c->out_rows_cap) return rv_fail(RV_E_ARG, "M exceeds the LM-head rows");
@@ -1193,7 +1215,7 @@ rv_status rv_debug_linear(const rv_cache* c, int32_t layer, int32_t matrix, cons
   g.Y = d_y;
   g.ldy = md->N;
   g.md = *md;
-  HIP_TRY(run_gemm(c, EPI_STORE_LOGICAL, g, false, st), "linear");
+  HIP_TRY(run_gemm(c, EPI_STORE_LOGICAL, g, plan_mat(c, EPI_STORE_LOGICAL, g.M, g.N, g.K, false), st), "linear");
   return RV_OK;
 }
 

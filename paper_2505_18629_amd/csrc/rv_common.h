@@ -183,6 +183,18 @@ RV_DEV __host__ inline size_t mat_packed_offset(const MatDesc& m, int p, int k, 
   return (((size_t)(p >> 4) * ksteps + tile_k) * 1024) + (size_t)lane * 16 + (size_t)j * es;
 }
 
+// ---------------------------------------------------------------- work items
+
+// Item of workgroup b in a launch of `items` rounded up to a multiple of 8
+// workgroups.  Workgroup b runs on XCD b % 8; each XCD gets one contiguous run
+// of ceil(items / 8) items, so items that share data stay behind one L2 and
+// the XCDs (32 CUs each) carry equal shares.  Results past `items` have no
+// work.
+RV_DEV int xcd_item(int b, int items) {
+  const int per = (items + 7) / 8;
+  return b % 8 * per + b / 8;
+}
+
 // ---------------------------------------------------------------- reductions
 
 // Reductions over the four lanes that share l % 16 (l, l^16, l^32, l^48) with

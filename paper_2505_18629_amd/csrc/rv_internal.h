@@ -59,11 +59,20 @@ struct GemmArgs {
 // nt: row tiles per workgroup (1, 2, 4 or 8, and 3 or 6 for EPI_PARTIAL; even for SWIGLU);
 // mtt: token tiles (1, 2, 4; 1 or 2 with nt = 8).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int mtt, hipStream_t st);
-// bf16, many tokens: nw*nt*16 rows x mt*16 tokens per workgroup of nw waves ((nw, nt, mt)
-// one of (8, 4, 8), (8, 4, 4), (8, 2, 8), (8, 2, 4), (8, 2, 6), (12, 2, 4)), n_tg = ceil(M / (mt*16))
-// token groups; N % (16*nw*nt) == 0; gk k-groups of a multiple of 4 k-steps each (gk > 1
-// only with EPI_PARTIAL).
-hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, int nw, int nt, int mt, hipStream_t st);
+// bf16, 33 rows and more: 256 (rows256) or 128 output rows x mt (2 - 9) token tiles per
+// workgroup, n_tg = ceil(M / (16*mt)) token groups; N a multiple of the rows, K/32 of gk
+// (of 2*gk without rows256); gk > 1 only with EPI_PARTIAL.
+hipError_t launch_gemm_wide(int epi, const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+// its instantiations, one file each
+hipError_t launch_wide_store(const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+hipError_t launch_wide_resid(const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+hipError_t launch_wide_partial(const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+hipError_t launch_wide_swiglu(const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+hipError_t launch_wide_qkv(const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+hipError_t launch_wide_store_logical(const GemmArgs& a, bool rows256, int mt, hipStream_t st);
+// bf16, large row counts: 512 output rows x 128 tokens per workgroup, n_tg = ceil(M / 128)
+// token groups; N % 512 == 0, (K/32) % 4 == 0, gk == 1, not EPI_PARTIAL.
+hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, hipStream_t st);
 
 // ---------------------------------------------------------------- attention
 // Query rows of one pass are grouped in segments (one per sequence and

@@ -3,13 +3,14 @@
 // the same code also builds for the CPU alone (the host checks under tests/).
 #pragma once
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 
 enum { RV_MAX_SEGS = 128 };   // query segments of one prefill chunk
 
 constexpr int kPrefillRows = 2048;    // rows per prefill chunk
 constexpr int kMaxSplitK = 16;        // k-groups of a split matmul
-constexpr int kMaxSplitTiled = 4;     // k-groups of a split many-token matmul
+constexpr int kMaxSplitTiled = 4;     // k-groups of a split matmul of a whole verify block that the partial buffer holds
 constexpr int kSplitRows = 64;        // matmuls with at most this many rows may split K
 constexpr int kSplitsPerQuery = 8;    // attention partial-buffer depth per query row
 constexpr int kMaxKeySplits = 64;     // key splits the combine kernel merges per query
@@ -99,6 +100,72 @@ inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* se
   return ks;
 }
 
+// Launch shape of a matmul on the wide kernel (k_wide.h): 256 or 128 output
+// rows x mt token tiles per workgroup, n_tg token groups, gk k-groups.
+struct WidePlan {
+  bool use;      // false: plan_matmul has the launch
+  bool rows256;
+  int mt, n_tg, gk;
+};
+
+constexpr int kWideMinRows = 33;  // fewer rows: the few-row kernel
+
+// Estimated time (us) of one matmul whose workgroups own `rows` output rows x
+// mt token tiles, `step` us per k-step.  Three limits overlap, combined as a
+// 4-norm: the workgroups' own steps (each XCD -- 32 CUs, one workgroup per CU
+// -- takes an equal share of them in whole rounds), the data (weights from HBM
+// once at 6.2 TB/s, every workgroup's operand rows from L2 at 27 TB/s) and
+// MFMA power (1.76 PFLOP/s of hi/lo products).  k-group partials are written
+// at 3.3 and read by the consumer at 5 TB/s.  Fitted to 5600 launches: 16
+// matrices (1B, 8B, 14B, 70B) and the LM heads at 20 - 2047 rows, every shape
+// and k-group count; error 9% rms, and the shape it picks costs 1.5% more
+// than the best one in the mean, 25% at worst (a 10 us launch).
+inline double plan_matmul_us(double step, int rows, int mt, int M, int N, int K, int gk, double split_us) {
+  const int n_tg = (M + 16 * mt - 1) / (16 * mt);
+  const long long items = (long long)(N / rows) * gk * n_tg;
+  const long long rounds = ((items + 7) / 8 + 31) / 32;
+  const double work = 0.57 + (double)rounds * (0.71 + step * (K / 32 / gk));
+  const double data = 3.5 + (double)N * K * 2 / 6.2e6 + (double)items * mt * 16 * (K / gk) * 4 / 2.7e7;
+  const double power = 4.0 * n_tg * mt * 16 * N * K / 1.76e9;
+  const double w2 = work * work, d2 = data * data, p2 = power * power;
+  const double t = std::sqrt(std::sqrt(w2 * w2 + d2 * d2 + p2 * p2));
+  return gk == 1 ? t : t + split_us + (double)gk * M * N * 4 * (1 / 3.3e6 + 1 / 5e6);
+}
+
+// bf16 matmuls of 33 rows and more: the cheapest of the wide kernel's shapes,
+// or use = false where the 512-row kernel costs less (hundreds of rows that
+// fill its 512 x 128 tiles: 8B gate/up at 496 tokens 184 against 195 us) or
+// no shape divides the matrix.  split_us: cost of splitting K beyond the
+// partials' traffic (the QKV projection then needs its finish kernel).
+inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, double split_us = 0) {
+  WidePlan p{};
+  if (M < kWideMinRows || N % 128) return p;
+  const int ksteps = K / 32;
+  double best = 0;
+  for (int r = 0; r < 2; ++r) {
+    const bool r256 = r == 1;
+    const int rows = r256 ? 256 : 128, kw = r256 ? 1 : 2;
+    if (N % rows) continue;
+    for (int mt = 2; mt <= 9; ++mt) {
+      // us per k-step of a workgroup: 16 row tiles on 4 waves, or 8 on 4 x 2
+      const double step = r256 ? 0.2886 + 0.0334 * mt : 0.1133 + 0.0306 * mt;
+      for (int gk : {1, 2, 3, 4, 6, 7, 8}) {
+        if (gk > 1 && (!allow_split || gk * M > part_rows)) break;
+        if (ksteps % (gk * kw)) continue;
+        const double t = plan_matmul_us(step, rows, mt, M, N, K, gk, split_us);
+        if (!p.use || t < best) {
+          best = t;
+          p = WidePlan{true, r256, mt, (M + 16 * mt - 1) / (16 * mt), gk};
+        }
+      }
+    }
+  }
+  // the 512-row kernel where it fills its rounds: about 3% under two rounds of
+  // 256 rows (8B gate/up at 1024 tokens 373 against 383 us)
+  if (p.use && N % 512 == 0 && ksteps % 4 == 0 && plan_matmul_us(1.07, 512, 8, M, N, K, 1, 0) < best) p.use = false;
+  return p;
+}
+
 // Launch shape of one matmul: row tiles per workgroup (nt), token tiles
 // (mtt), token groups and k-groups.  Aims for >= 384 workgroups (1.5 per CU)
 // with as many rows per workgroup as possible, since every workgroup reads
@@ -106,11 +173,13 @@ inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* se
 // residual-stream outputs of few-row passes (the next RMSNorm adds the
 // partials).
 struct GemmPlan {
-  bool tiled;  // many-token kernel (launch_gemm_tiled)
+  bool tiled;  // 512-row kernel (launch_gemm_tiled)
   int nt, mtt, n_tg, gk;
-  int nw;      // waves per workgroup of the many-token kernel
+  int nw;      // waves per workgroup of the 512-row kernel
 };
 
+// The matmuls plan_wide leaves: up to 32 rows, fp32, and the large ones of the
+// 512-row kernel.
 // part_rows: capacity of the partial buffer in rows (gk * M must fit);
 // bf16: the element type (k-steps of 32, else 16); swiglu: gate/up tile pairs.
 inline GemmPlan plan_matmul(bool bf16, bool swiglu, int M, int N, int K, bool allow_split, int part_rows) {
@@ -118,57 +187,7 @@ inline GemmPlan plan_matmul(bool bf16, bool swiglu, int M, int N, int K, bool al
   const int ksteps = K / (bf16 ? 32 : 16);
   GemmPlan p{};
   p.gk = 1;
-  // Many tokens (bf16): the LDS-tiled kernel (one 8- or 12-wave workgroup per CU)
-  // streams the weights about once for all token groups.  The shape is
-  // chosen to minimise (rounds of 256 workgroups) x (work per workgroup),
-  // ties broken as below (measured over the 8B, 14B and 70B matrices at
-  // 172-496 tokens: within 6% of the best of every shape tried).  K is split only for outputs whose
-  // consumer adds k-group partials.
-  if (bf16 && M > kSplitRows && N % 256 == 0) {
-    p.tiled = true;
-    long long best_cost = -1, best_wgs = 0;
-    // (waves, row tiles per wave, token tiles).  A workgroup's time goes as
-    // its waves per SIMD times each wave's work.  Twelve waves (three per
-    // SIMD, two row tiles each) give 3/4 of the 8-wave 4 x 4 workgroup's
-    // work, for matrices whose 8-wave split leaves CUs idle in a single round
-    // (14B gate/up at 172 tokens: 162 -> 216 workgroups); six token tiles
-    // do the same for widths that twelve waves do not divide (14B QKV at
-    // 172 tokens: 168 -> 224 workgroups, 39.8 -> 35.3 us).  Equal costs go
-    // to fewer workgroups, then more row tiles per wave (each staged operand
-    // tile feeds that many MFMAs, so 4 row tiles need half the LDS reads per
-    // MFMA of 2: O and down as 4 x 4 instead of 2 x 8, 8B batch 16 17.91 ->
-    // 17.76 ms, 70B 126.9 -> 124.9 ms), then more waves per workgroup (the
-    // 14B gate/up: 12 waves x 4 token tiles 104 us, 8 waves x 6 token tiles
-    // 108 us), then larger tiles.
-    const int shapes[][3] = {{8, 4, 8}, {8, 2, 8}, {8, 4, 4}, {8, 2, 4}, {12, 2, 4}, {8, 2, 6}};
-    for (const auto& sh : shapes) {
-      const int nw = sh[0], nt = sh[1], mt = sh[2];
-      if (N % (16 * nw * nt)) continue;
-      const int n_tg = (M + 16 * mt - 1) / (16 * mt);
-      for (int gk = 1; gk <= (allow_split ? kMaxSplitTiled : 1); gk *= 2) {
-        if (ksteps % gk || (ksteps / gk) % 4 || (gk > 1 && gk * M > part_rows)) continue;
-        const long long wgs = (long long)(N / (16 * nw * nt)) * gk * n_tg;
-        if (nw == 12 && wgs > 256) continue;
-        const long long cost = (wgs + 255) / 256 * nw * nt * mt * (ksteps / gk);
-        const bool better = best_cost < 0 || cost < best_cost || (cost == best_cost && wgs < best_wgs) ||
-                            (cost == best_cost && wgs == best_wgs && nt > p.nt) ||
-                            (cost == best_cost && wgs == best_wgs && nt == p.nt && nw > p.nw) ||
-                            (cost == best_cost && wgs == best_wgs && nt == p.nt && nw == p.nw && nt * mt > p.nt * p.mtt);
-        if (better) {
-          best_cost = cost;
-          best_wgs = wgs;
-          p.nw = nw;
-          p.nt = nt;
-          p.mtt = mt;
-          p.n_tg = n_tg;
-          p.gk = gk;
-        }
-      }
-    }
-    if (best_cost >= 0) return p;
-    p.tiled = false;
-    p.gk = 1;
-  }
+  if (bf16 && M > kSplitRows && N % 512 == 0 && ksteps % 4 == 0) return GemmPlan{true, 4, 8, (M + 127) / 128, 1, 8};
   p.mtt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
   p.n_tg = (M + 16 * p.mtt - 1) / (16 * p.mtt);
   const int nt_min = swiglu ? 2 : 1;
