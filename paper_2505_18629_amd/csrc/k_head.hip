@@ -69,7 +69,12 @@ RV_DEV float uniform23(uint64_t w) { return ((float)(w >> 41) + 0.5f) * (1.0f / 
 
 // Sequence b of fused row r and the row's index i within it (sequence b owns
 // rows b + K_b .. b + K_b + k_b).
-RV_DEV void fused_row_seq(const uint8_t* kb, int B, int r, int& b, int& i) {
+RV_DEV void fused_row_seq(const uint8_t* kb, int uniform, int B, int r, int& b, int& i) {
+  if (uniform >= 0) {
+    b = r / (uniform + 1);
+    i = r - b * (uniform + 1);
+    return;
+  }
   int start = 0;
   for (b = 0; b < B - 1; ++b) {
     const int n = kb[b] + 1;
@@ -102,25 +107,47 @@ RV_DEV Stat stat_merge(Stat a, Stat b) {
   return r;
 }
 
-RV_DEV Stat stat_shfl(Stat a, int off) {
-  return Stat{__shfl_xor(a.m, off, 64), __shfl_xor(a.s, off, 64), __shfl_xor(a.s1, off, 64)};
+// Statistics of the wave's 64 x E values; entries that are not there are -inf.
+// One maximum for the whole wave first, so that every value is exponentiated
+// once and the sums need no rescaling.
+template <int E>
+RV_DEV Stat wave_stat(const float (&x)[E]) {
+  float m = -INFINITY;  // stays below every value if all are NaN
+#pragma unroll
+  for (int e = 0; e < E; ++e) m = fmaxf(m, x[e]);
+  Stat r{wave_max(m), 0.f, 0.f};
+  if (r.m == -INFINITY) return r;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const float d = x[e] - r.m, p = __expf(d);
+    r.s += p;
+    r.s1 += p > 0.f ? p * d : 0.f;  // 0 log 0 = 0 (ids at -inf)
+  }
+  r.s = wave_sum(r.s);
+  r.s1 = wave_sum(r.s1);
+  return r;
 }
 
-template <int E>
-RV_DEV Stat stat_of(const float (&x)[E], int n_valid) {
-  float m = -INFINITY;
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (e < n_valid) m = fmaxf(m, x[e]);
-  Stat r{m, 0.f, 0.f};
-  if (m == -INFINITY) return r;
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (e < n_valid) {
-      const float d = x[e] - m, p = __expf(d);
-      r.s += p;
-      r.s1 += p > 0.f ? p * d : 0.f;  // 0 log 0 = 0 (ids at -inf)
-    }
+// Merge of one set per lane (empty: m = -inf).
+RV_DEV Stat wave_merge(Stat a) {
+  Stat r{wave_max(a.m), 0.f, 0.f};
+  if (r.m == -INFINITY) return r;
+  if (a.m != -INFINITY) {
+    const float d = a.m - r.m, e = __expf(d);
+    r.s = a.s * e;
+    r.s1 = e * (a.s1 + a.s * d);
+  }
+  r.s = wave_sum(r.s);
+  r.s1 = wave_sum(r.s1);
+  return r;
+}
+
+// Merge of one Top per lane (indices differ between lanes that hold values).
+RV_DEV Top wave_merge(Top a) {
+  Top r;
+  r.m1 = wave_max(a.m1);
+  r.i1 = wave_min(a.m1 == r.m1 ? a.i1 : 0x7fffffff);
+  r.m2 = wave_max(a.m1 == r.m1 && a.i1 == r.i1 ? a.m2 : a.m1);
   return r;
 }
 
@@ -138,30 +165,49 @@ RV_DEV float fused_at(const HeadArgs& a, int row, int lrow_o, int lrow_r, int v)
 }
 
 // One workgroup per (vocabulary chunk of 2048, fused row); each thread owns 8
-// entries, strided by 256, and loads them all before computing.
+// entries and loads them all before computing: with VEC two runs of 4
+// consecutive ids (16-byte loads; rows of a multiple of 4 ids, 16-byte aligned),
+// else single ids strided by 256.  A launch is a few microseconds of latency
+// per workgroup above its traffic, so the reductions decide: with a running
+// (max, sum, sum) merge of every pair of lanes, two exponentials and five LDS
+// shuffles each, 24 rows of 128256 took 16.6 us; one wave maximum first and
+// plain DPP sums take 9.8 us (288 logit rows 53 -> 31 us, 4.7 TB/s).
+template <bool VEC>
 __global__ __launch_bounds__(256) void k_fuse_stats(HeadArgs a) {
   constexpr int E = 8;
   const int chunk = blockIdx.x, row = blockIdx.y;  // fused row
   int b, i;
-  fused_row_seq(a.kb, a.B, row, b, i);
+  fused_row_seq(a.kb, a.kb_uni, a.B, row, b, i);
   const int k1 = a.kb[b] + 1, lrow0 = 2 * (row - i);  // first logit row of sequence b
   const float* o = a.logits + ((size_t)lrow0 + i) * a.V;
   const float* r = a.logits + ((size_t)lrow0 + k1 + i) * a.V;
   float* z = a.z ? a.z + (size_t)row * a.V : nullptr;  // fused rows kept for inspection
   const float wa = a.alpha, wo = 1.0f - a.alpha;
   const int v0 = chunk * a.chunk, v1 = min(a.V, v0 + a.chunk);
+  // id of entry e (increasing with e)
+  auto id = [&](int e) {
+    return VEC ? v0 + (int)threadIdx.x * 4 + (e >> 2) * 1024 + (e & 3) : v0 + (int)threadIdx.x + e * 256;
+  };
   float ov[E], rv[E], zv[E];
+  if constexpr (VEC) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int v = min(v0 + threadIdx.x + e * 256, v1 - 1);
-    ov[e] = o[v];
-    rv[e] = r[v];
+    for (int u = 0; u < 2; ++u) {
+      const int v = min(id(4 * u), v1 - 4);  // v1 is a multiple of 4
+      const f32x4_t x = *(const f32x4_t*)(o + v), y = *(const f32x4_t*)(r + v);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ov[4 * u + e] = x[e];
+        rv[4 * u + e] = y[e];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int v = min(id(e), v1 - 1);
+      ov[e] = o[v];
+      rv[e] = r[v];
+    }
   }
-  // entries e < n_valid are inside the chunk (v increases with e)
-  const int n_valid = min(E, max(0, (v1 - v0 - (int)threadIdx.x + 255) / 256));
-  // start from a valid id, so the argmax stays in the vocabulary even if
-  // no value compares greater (NaN logits)
-  Top t{-INFINITY, v0, -INFINITY};
   const bool tempered = a.temp != 1.0f;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -169,27 +215,35 @@ __global__ __launch_bounds__(256) void k_fuse_stats(HeadArgs a) {
     const float zr = wa * rv[e];
     zv[e] = zo + zr;
     if (tempered) zv[e] = zv[e] / a.temp;
-    if (e < n_valid) {
-      const int v = v0 + threadIdx.x + e * 256;
-      if (z) z[v] = zv[e];
-      if (zv[e] > t.m1) {
-        t.m2 = t.m1;
-        t.m1 = zv[e];
-        t.i1 = v;
-      } else if (zv[e] > t.m2) {
-        t.m2 = zv[e];
-      }
+  }
+  if (z) {
+    if constexpr (VEC) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (id(4 * u) < v1) *(f32x4_t*)(z + id(4 * u)) = f32x4_t{zv[4 * u], zv[4 * u + 1], zv[4 * u + 2], zv[4 * u + 3]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (id(e) < v1) z[id(e)] = zv[e];
     }
   }
-  Stat so = stat_of(ov, n_valid), sr = stat_of(rv, n_valid), sz = stat_of(zv, n_valid);
-  // wave reduction then LDS across the 4 waves
-  for (int off = 32; off > 0; off >>= 1) {
-    so = stat_merge(so, stat_shfl(so, off));
-    sr = stat_merge(sr, stat_shfl(sr, off));
-    sz = stat_merge(sz, stat_shfl(sz, off));
-    Top u{__shfl_xor(t.m1, off, 64), __shfl_xor(t.i1, off, 64), __shfl_xor(t.m2, off, 64)};
-    t = top_merge(t, u);
-  }
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (id(e) >= v1) ov[e] = rv[e] = zv[e] = -INFINITY;
+  const Stat so = wave_stat(ov), sr = wave_stat(rv), sz = wave_stat(zv);
+  // z's maximum, its lowest id, and the largest other value; where nothing
+  // compares greater than -inf (or all is NaN) the chunk's first id, so that
+  // the argmax stays in the vocabulary
+  Top t{sz.m, 0x7fffffff, -INFINITY};
+#pragma unroll
+  for (int e = E - 1; e >= 0; --e)
+    if (zv[e] == t.m1) t.i1 = id(e);
+  t.i1 = t.m1 == -INFINITY ? v0 : wave_min(t.i1);
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (id(e) != t.i1) t.m2 = fmaxf(t.m2, zv[e]);
+  t.m2 = wave_max(t.m2);
+  // the 4 waves in LDS
   __shared__ Stat sh_st[4][3];
   __shared__ Top sh_top[4];
   const int w = threadIdx.x >> 6;
@@ -200,27 +254,20 @@ __global__ __launch_bounds__(256) void k_fuse_stats(HeadArgs a) {
     sh_top[w] = t;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int ww = 1; ww < 4; ++ww) {
-      so = stat_merge(so, sh_st[ww][0]);
-      sr = stat_merge(sr, sh_st[ww][1]);
-      sz = stat_merge(sz, sh_st[ww][2]);
-      t = top_merge(t, sh_top[ww]);
+  // threads 0..2 merge one statistic each, thread 3 the maxima
+  const int f = threadIdx.x;
+  if (f < 4) {
+    f32x4_t out;
+    if (f < 3) {
+      Stat st = sh_st[0][f];
+      for (int ww = 1; ww < 4; ++ww) st = stat_merge(st, sh_st[ww][f]);
+      out = f32x4_t{st.m, st.s, st.s1, 0.f};
+    } else {
+      Top tt = sh_top[0];
+      for (int ww = 1; ww < 4; ++ww) tt = top_merge(tt, sh_top[ww]);
+      out = f32x4_t{__int_as_float(tt.i1), tt.m1, tt.m2, 0.f};
     }
-    const int R1 = a.R1;
-    const Stat st[3] = {so, sr, sz};
-    for (int f = 0; f < 3; ++f) {
-      float* p = a.part + ((size_t)(f * R1 + row) * a.nchunk + chunk) * 4;
-      p[0] = st[f].m;
-      p[1] = st[f].s;
-      p[2] = st[f].s1;
-      p[3] = 0.f;
-    }
-    float* p = a.part + ((size_t)(3 * R1 + row) * a.nchunk + chunk) * 4;
-    p[0] = __int_as_float(t.i1);
-    p[1] = t.m1;
-    p[2] = t.m2;
-    p[3] = 0.f;
+    *(f32x4_t*)(a.part + ((size_t)(f * a.R1 + row) * a.nchunk + chunk) * 4) = out;
   }
 }
 
@@ -230,7 +277,7 @@ __global__ __launch_bounds__(256) void k_fuse_stats(HeadArgs a) {
 // the rule.
 __global__ __launch_bounds__(512) void k_accept(HeadArgs a) {
   const int b = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int kb = a.kb[b], k1 = kb + 1, R1 = a.R1, Kb = kb_prefix(a.kb, b);
+  const int kb = a.kb[b], k1 = kb + 1, R1 = a.R1, Kb = kb_prefix(a.kb, b, a.kb_uni);
   const int zrow0 = b + Kb;  // first fused row of sequence b
   const int* x = a.drafts + (size_t)b * a.k;
   __shared__ int xhat[RV_MAX_DRAFTS + 1];
@@ -260,18 +307,16 @@ __global__ __launch_bounds__(512) void k_accept(HeadArgs a) {
     Stat st[3] = {{-INFINITY, 0.f, 0.f}, {-INFINITY, 0.f, 0.f}, {-INFINITY, 0.f, 0.f}};
     Top t{-INFINITY, 0x7fffffff, -INFINITY};
     for (int c = lane; c < a.nchunk; c += 64) {
-      for (int f = 0; f < 3; ++f) {
-        const float* p = a.part + ((size_t)(f * R1 + row) * a.nchunk + c) * 4;
-        st[f] = stat_merge(st[f], Stat{p[0], p[1], p[2]});
-      }
-      const float* pt = a.part + ((size_t)(3 * R1 + row) * a.nchunk + c) * 4;
-      t = top_merge(t, Top{pt[1], __float_as_int(pt[0]), pt[2]});
+      f32x4_t p[4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) p[f] = *(const f32x4_t*)(a.part + ((size_t)(f * R1 + row) * a.nchunk + c) * 4);
+#pragma unroll
+      for (int f = 0; f < 3; ++f) st[f] = stat_merge(st[f], Stat{p[f][0], p[f][1], p[f][2]});
+      t = top_merge(t, Top{p[3][1], __float_as_int(p[3][0]), p[3][2]});
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      for (int f = 0; f < 3; ++f) st[f] = stat_merge(st[f], stat_shfl(st[f], off));
-      Top u{__shfl_xor(t.m1, off, 64), __shfl_xor(t.i1, off, 64), __shfl_xor(t.m2, off, 64)};
-      t = top_merge(t, u);
-    }
+#pragma unroll
+    for (int f = 0; f < 3; ++f) st[f] = wave_merge(st[f]);
+    t = wave_merge(t);
     if (lane == 0) {
       for (int f = 0; f < 3; ++f) a.lse[f * R1 + row] = st[f].m + logf(st[f].s);
       // entropy of the softmax: log S - S1 / S in the centred form
@@ -285,7 +330,8 @@ __global__ __launch_bounds__(512) void k_accept(HeadArgs a) {
       t.i1 = min(max(t.i1, 0), a.V - 1);  // every id used as an index below is in range
       xhat[i] = t.i1;
       top2[i] = t.m2;
-      zh[i] = fused_at(a, row, lrow_o, lrow_r, t.i1);
+      // the maximum is that id's fused logit (reloaded where no value compared greater)
+      zh[i] = t.m1 > -INFINITY ? t.m1 : fused_at(a, row, lrow_o, lrow_r, t.i1);
       a.argmax[row] = t.i1;
       if (i < kb) {
         xs[i] = xi;
@@ -375,7 +421,7 @@ __global__ __launch_bounds__(256) void k_sample(HeadArgs a) {
   const int chunk = blockIdx.x, b = blockIdx.y;
   const int n = a.accept_len[b];
   if (n < 0) return;
-  const int R1 = a.R1, row = b + kb_prefix(a.kb, b) + n;
+  const int R1 = a.R1, row = b + kb_prefix(a.kb, b, a.kb_uni) + n;
   const float* z = a.z + (size_t)row * a.V;
   const float lse = a.lse[2 * R1 + row];
   const float* q = n < a.kb[b] ? a.q + ((size_t)b * a.k + n) * a.V : nullptr;
@@ -409,10 +455,7 @@ __global__ __launch_bounds__(256) void k_sample(HeadArgs a) {
       }
     }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    Top o{__shfl_xor(t.m1, off, 64), __shfl_xor(t.i1, off, 64), __shfl_xor(t.m2, off, 64)};
-    t = top_merge(t, o);
-  }
+  t = wave_merge(t);
   __shared__ Top sh[4];
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) sh[w] = t;
@@ -433,16 +476,13 @@ __global__ __launch_bounds__(64) void k_sample_finish(HeadArgs a) {
   const int b = blockIdx.x, lane = threadIdx.x;
   const int n = a.accept_len[b];
   if (n < 0) return;
-  const int R1 = a.R1, row = b + kb_prefix(a.kb, b) + n;
+  const int R1 = a.R1, row = b + kb_prefix(a.kb, b, a.kb_uni) + n;
   Top t{-INFINITY, 0x7fffffff, -INFINITY};
   for (int c = lane; c < a.nchunk; c += 64) {
     const float* p = a.part + ((size_t)(3 * R1 + row) * a.nchunk + c) * 4;
     t = top_merge(t, Top{p[1], __float_as_int(p[0]), p[2]});
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    Top o{__shfl_xor(t.m1, off, 64), __shfl_xor(t.i1, off, 64), __shfl_xor(t.m2, off, 64)};
-    t = top_merge(t, o);
-  }
+  t = wave_merge(t);
   if (lane != 0) return;
   const int tok = min(max(t.i1, 0), a.V - 1);
   a.next_id[b] = tok;
@@ -460,7 +500,7 @@ __global__ __launch_bounds__(256) void k_logprob(HeadArgs a) {
   const int R1 = a.R1;
   const int f = fr / R1, row = fr % R1;
   int b, i;
-  fused_row_seq(a.kb, a.B, row, b, i);
+  fused_row_seq(a.kb, a.kb_uni, a.B, row, b, i);
   const int k1 = a.kb[b] + 1;
   const float* src = f == 2 ? a.z + (size_t)row * a.V
                             : a.logits + ((size_t)2 * (row - i) + (f == 1 ? k1 : 0) + i) * a.V;
@@ -493,7 +533,11 @@ hipError_t launch_exp(const float* src, float* dst, size_t n, hipStream_t st) {
 
 hipError_t launch_head(const HeadArgs& a, hipStream_t st) {
   const int R1 = a.R1;
-  k_fuse_stats<<<dim3(a.nchunk, R1), 256, 0, st>>>(a);
+  // 16-byte accesses need rows of whole float4s (the vocabulary may be any
+  // size where the caller gives the logits) at 16-byte addresses
+  const bool vec = a.V % 4 == 0 && ((uintptr_t)a.logits | (uintptr_t)a.z) % 16 == 0;
+  if (vec) k_fuse_stats<true><<<dim3(a.nchunk, R1), 256, 0, st>>>(a);
+  else k_fuse_stats<false><<<dim3(a.nchunk, R1), 256, 0, st>>>(a);
   k_accept<<<a.B, 512, 0, st>>>(a);
   if (a.rule == RV_RULE_SAMPLING) {
     k_sample<<<dim3(a.nchunk, a.B), 256, 0, st>>>(a);

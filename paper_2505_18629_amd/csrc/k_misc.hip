@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void k_plan_verify(PlanVerify p) {
   const int j = blockIdx.x, b = blockIdx.y;
   const int k = p.kb[b], S = 1 + 2 * k + p.n_probe + p.P;
   if (j >= S) return;
-  const int Kb = kb_prefix(p.kb, b);
+  const int Kb = kb_prefix(p.kb, b, p.kb_uni);
   const int row0 = b * (1 + p.n_probe + p.P) + 2 * Kb;  // first block row of sequence b
   const int L = p.L[b];
   const int* hist = p.ids + (size_t)b * p.max_len;

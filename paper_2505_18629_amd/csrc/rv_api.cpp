@@ -730,6 +730,7 @@ HeadArgs head_args(rv_cache* c, int k, const uint8_t* kb, int R1, int n_probe, i
   ha.P = P;
   ha.R1 = R1;
   for (int b = 0; b < c->B; ++b) ha.kb[b] = kb[b];
+  ha.kb_uni = kb_uniform(kb, c->B);
   ha.max_len = c->max_len;
   ha.nchunk = c->nchunk;
   ha.chunk = kVocabChunk;
@@ -830,6 +831,7 @@ rv_status verify_impl(rv_cache* c, const int32_t* h_prefix_len, const int32_t* d
   pv.k = k;
   pv.lm_src = c->lm_src;
   for (int b = 0; b < c->B; ++b) pv.kb[b] = kb[b];
+  pv.kb_uni = kb_uniform(kb, c->B);
   pv.n_probe = n_probe;
   pv.P = P;
   pv.d = mc.d_model;

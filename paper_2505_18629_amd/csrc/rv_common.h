@@ -217,11 +217,34 @@ RV_DEV float rows4_sum(float x) {
   return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
+// Reductions over the wave's 64 lanes, result in every lane: four DPP steps
+// inside each row of 16 (neighbour, pair, half-row mirror, row mirror), then
+// the row swaps above -- VALU work only, against six LDS-crossbar shuffles.
+template <int CTRL>
+RV_DEV uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+}
+template <typename F>
+RV_DEV uint32_t wave_reduce(uint32_t x, F op) {
+  x = op(x, dpp<0xB1>(x));   // quad_perm 1,0,3,2
+  x = op(x, dpp<0x4E>(x));   // quad_perm 2,3,0,1
+  x = op(x, dpp<0x141>(x));  // row_half_mirror
+  x = op(x, dpp<0x140>(x));  // row_mirror
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = op(r[0], r[1]);
+  const auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return op(s[0], s[1]);
+}
 RV_DEV float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return __uint_as_float(wave_reduce(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
 }
 RV_DEV float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return __uint_as_float(wave_reduce(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
+RV_DEV int wave_min(int v) {
+  return (int)wave_reduce((uint32_t)v, [](uint32_t a, uint32_t b) { return (uint32_t)min((int)a, (int)b); });
 }

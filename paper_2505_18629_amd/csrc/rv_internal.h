@@ -122,10 +122,18 @@ hipError_t launch_rmsnorm(int dtype, float* h, int rows, int d, const float* gai
 // Per-sequence draft counts k_b of a verify pass (uniform passes have k_b = k).
 // Block b has S_b = 1 + 2 k_b + n_probe + P rows from row b (1 + n_probe + P)
 // + 2 K_b, and k_b + 1 fused rows from row b + K_b, with K_b = sum_{b' < b} k_b'.
-RV_DEV inline int kb_prefix(const uint8_t* kb, int b) {
+// `uniform`: the draft count of every sequence, or -1 where they differ (the
+// counts are then summed one by one, a dependent load each).
+RV_DEV inline int kb_prefix(const uint8_t* kb, int b, int uniform) {
+  if (uniform >= 0) return b * uniform;
   int s = 0;
   for (int i = 0; i < b; ++i) s += kb[i];
   return s;
+}
+inline int kb_uniform(const uint8_t* kb, int B) {
+  for (int b = 1; b < B; ++b)
+    if (kb[b] != kb[0]) return -1;
+  return kb[0];
 }
 
 struct QkvFinish {
@@ -166,6 +174,7 @@ struct PlanVerify {
   int* seg_pos0;
   int L[RV_MAX_BATCH];
   uint8_t kb[RV_MAX_BATCH];
+  int kb_uni;            // kb_uniform(kb, B)
 };
 hipError_t launch_plan_verify(int dtype, const PlanVerify& p, hipStream_t st);
 
@@ -220,6 +229,7 @@ struct HeadArgs {
   int* argmax;           // [R1]
   int L[RV_MAX_BATCH];
   uint8_t kb[RV_MAX_BATCH];
+  int kb_uni;            // kb_uniform(kb, B)
 };
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);
 // dst[i] = exp(src[i]) for i < n.

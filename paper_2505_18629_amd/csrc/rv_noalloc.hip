@@ -88,6 +88,7 @@ extern "C" rv_status rv_fuse_accept_noalloc(const float* d_logits, int32_t batch
   a.V = vocab;
   a.R1 = R1;
   for (int b = 0; b < batch; ++b) a.kb[b] = (uint8_t)k;
+  a.kb_uni = k;
   a.nchunk = nchunk;
   a.chunk = kChunk;
   a.alpha = fusion->alpha;
