@@ -286,6 +286,189 @@ __global__ __launch_bounds__(NW * 64) void k_attn_bf16(AttnArgs a, int n_qg) {
   }
 }
 
+// ----------------------------------------------------------- bf16, few queries
+// At most 16 queries per (segment, kv head): decode steps (one row, G query
+// heads).  With the kernel above seven of the eight waves would have no query
+// tile and one would walk the keys alone (16 sequences of 300 - 1900 keys at
+// the 1B shape: 21.2 us per launch).  Here the waves share the 16 queries and
+// split the keys: wave w takes the split's tiles w, w + 8, ... of KT keys, reads
+// their K and V operands straight to registers (no other wave needs them), the
+// next tile's K while this tile's softmax runs and its V after the products
+// with this tile's, and the eight states merge in LDS.  With one split the
+// workgroup writes the attention output itself and no combine kernel follows.
+// Bound by the K/V stream (hi and lo planes of both): 3.7 TB/s over 16 ragged
+// sequences, 4.7 TB/s over 8 x 4000 keys at the 8B shape.  STREAM: nontemporal
+// loads, for launches that fill the 256 CUs, so that the stream does not push
+// other data out of L2 (1B pass, 32 x 1000 keys: 488 -> 468 us; 16 x 300 - 1900:
+// 1194 -> 1175); with fewer workgroups each CU's own rate counts, which they
+// lower (8B, 1 x 1024 keys: 7.6 -> 8.9 us per launch; 70B, 4 x 3000: 21 -> 28).  Passes before and after this kernel: 1B 32 x 1000
+// keys (4 layers) 579 -> 468 us, 16 x 300 - 1900 (16 layers) 1241 -> 1175.
+template <int HD, bool STREAM>
+__global__ __launch_bounds__(512) void k_attn_few(AttnArgs a) {
+  constexpr int KT = HD == 128 ? 32 : 64;  // keys per tile: 128 registers of operands
+  constexpr int NW = 8, NB = KT / 16, NC = KT / 32;
+  constexpr int DC = HD / 32, DT = HD / 16;
+  __shared__ __attribute__((aligned(16))) float red_o[NW][16][HD + 4];  // padded: 16 queries, 16 banks
+  __shared__ float red_m[NW][16], red_l[NW][16];
+  const int grp = blockIdx.x, split = blockIdx.y;
+  const int seg = grp / a.n_kv, kvh = grp % a.n_kv;
+  const int G = a.n_heads / a.n_kv;
+  const int nrows = a.seg_n[seg], row0 = a.seg_row0[seg], pos0 = a.seg_pos0[seg], b = a.seg_b[seg];
+  const int Q = G * nrows;
+  const int kmax = pos0 + (Q - 1) / G + 1;
+  const int kbeg = split * a.ks, kend = min(kmax, kbeg + a.ks);
+  if (kbeg >= kend) return;  // no query of the segment sees this split
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qd = a.n_heads * HD;
+  const size_t kvoff = (size_t)(b * a.n_kv + kvh) * a.kv_len * HD + lane * 8;
+  const uint16_t* kp[2] = {(const uint16_t*)a.kc + kvoff, (const uint16_t*)a.kc2 + kvoff};
+  const uint16_t* vp[2] = {(const uint16_t*)a.vc + kvoff, (const uint16_t*)a.vc2 + kvoff};
+
+  u32x4 k[2][NB][DC], v[2][NC][DT];
+  // The cache holds whole 64-key tiles, so a tile that starts below kend is
+  // inside it; tiles past the last load that one again and are not used.
+  const int last = kbeg + (kend - 1 - kbeg) / KT * KT;
+  auto load_kv = [](const uint16_t* p) {
+    return STREAM ? __builtin_nontemporal_load((const u32x4*)p) : *(const u32x4*)p;
+  };
+  auto load_k = [&](int k0) {
+    k0 = min(k0, last);
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+      for (int t = 0; t < NB; ++t)
+#pragma unroll
+        for (int c = 0; c < DC; ++c) k[pl][t][c] = load_kv(kp[pl] + (size_t)k0 * HD + (t * DC + c) * 512);
+  };
+  auto load_v = [&](int k0) {
+    k0 = min(k0, last);
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int d = 0; d < DT; ++d) v[pl][c][d] = load_kv(vp[pl] + (size_t)k0 * HD + (c * DT + d) * 512);
+  };
+  int k0 = kbeg + w * KT;
+  const bool any = k0 < kend;
+  if (any) {
+    load_k(k0);
+    load_v(k0);
+  }
+  const int q = lane & 15, qc = min(q, Q - 1), qpos = pos0 + qc / G;
+  uint4 qB[2][DC];
+#pragma unroll
+  for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+      qB[pl][c] = *(const uint4*)((const char*)(pl ? a.q2 : a.q) +
+                                  operand_offset(row0 + qc / G, (kvh * G + qc % G) * HD + 32 * c + g * 8, qd, 2));
+  float m = -INFINITY, l = 0.f;
+  f32x4_t O[DT];
+#pragma unroll
+  for (int d = 0; d < DT; ++d) O[d] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  for (; k0 < kend; k0 += NW * KT) {
+    f32x4_t s[NB];
+#pragma unroll
+    for (int t = 0; t < NB; ++t) s[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < DC; ++c) {
+      const bf16x8_t qh = __builtin_bit_cast(bf16x8_t, qB[0][c]), ql = __builtin_bit_cast(bf16x8_t, qB[1][c]);
+#pragma unroll
+      for (int t = 0; t < NB; ++t)
+        s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k[0][t][c]), qh, s[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NB; ++t)
+        s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k[0][t][c]), ql, s[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NB; ++t)
+        s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k[1][t][c]), qh, s[t], 0, 0, 0);
+    }
+    load_k(k0 + NW * KT);
+    const float sc = a.scale_log2;
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int key = k0 + 16 * t + 4 * g + i;
+        if (!(key < kend && key <= qpos)) s[t][i] = -INFINITY;
+        mloc = fmaxf(mloc, s[t][i]);
+      }
+    mloc = rows4_max(mloc);
+    const float m_new = fmaxf(m, mloc * sc);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float rescale = __builtin_amdgcn_exp2f(m - m_use);
+    float psum = 0.f;
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[t][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][i], sc, -m_use));
+        psum += s[t][i];
+      }
+    l = l * rescale + rows4_sum(psum);
+    m = m_new;
+#pragma unroll
+    for (int d = 0; d < DT; ++d) O[d] *= rescale;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      bf16x8_t phi, plo;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float p = j < 4 ? s[2 * c][j] : s[2 * c + 1][j - 4];
+        const uint16_t hb = f2bf(p);
+        phi[j] = __builtin_bit_cast(__bf16, hb);
+        plo[j] = __builtin_bit_cast(__bf16, f2bf(p - bf2f(hb)));
+      }
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+        O[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v[0][c][d]), phi, O[d], 0, 0, 0);
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+        O[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v[0][c][d]), plo, O[d], 0, 0, 0);
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+        O[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v[1][c][d]), phi, O[d], 0, 0, 0);
+    }
+    load_v(k0 + NW * KT);
+  }
+
+  // merge the waves: a wave without tiles has m = -inf, l = 0, O = 0
+#pragma unroll
+  for (int d = 0; d < DT; ++d) *(f32x4_t*)&red_o[w][q][16 * d + 4 * g] = O[d];
+  if (g == 0) {
+    red_m[w][q] = m;
+    red_l[w][q] = l;
+  }
+  __syncthreads();
+  const int oq = tid / (HD / 4), od = tid % (HD / 4) * 4;  // this thread's query and 4 dims
+  if (oq >= min(Q, 16)) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) M = fmaxf(M, red_m[i][oq]);
+  float L = 0.f;
+  f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const float f = red_m[i][oq] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(red_m[i][oq] - M);
+    L += red_l[i][oq] * f;
+    x += *(const f32x4_t*)&red_o[i][oq][od] * f;
+  }
+  if (a.nsplit == 1) {
+    put_operand4<RV_BF16>(a.out, a.out2, row0 + oq / G, (kvh * G + oq % G) * HD + od, qd, x * (1.0f / L));
+    return;
+  }
+  const size_t e = ((size_t)split * (a.nseg * a.n_kv) + grp) * a.qmax + oq;
+  *(f32x4_t*)(a.part_o + e * HD + od) = x;
+  if (od == 0) {
+    a.part_ml[2 * e] = M;
+    a.part_ml[2 * e + 1] = L;
+  }
+}
+
 // ----------------------------------------------------------- fp32, MFMA
 // One wave per (16 queries, key split, kv head), 8 waves to a workgroup, on
 // 16x16x4 fp32 MFMAs, with the bf16 kernel's tile structure and partial
@@ -518,7 +701,26 @@ hipError_t launch_export_kv(const void* src_hi, const void* src_lo, int hd, int 
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, int n_qgroups, int qpw, hipStream_t st) {
   const int groups = a.nseg * a.n_kv;
-  if (dtype == RV_BF16) {
+  if (dtype == RV_BF16 && qpw == 16) {
+    if (a.qmax > 16) return hipErrorInvalidValue;
+    const dim3 grid(groups, a.nsplit);
+    const bool stream = groups * a.nsplit >= 256;
+    switch (a.hd) {
+      case 32:
+        if (stream) k_attn_few<32, true><<<grid, 512, 0, st>>>(a);
+        else k_attn_few<32, false><<<grid, 512, 0, st>>>(a);
+        break;
+      case 64:
+        if (stream) k_attn_few<64, true><<<grid, 512, 0, st>>>(a);
+        else k_attn_few<64, false><<<grid, 512, 0, st>>>(a);
+        break;
+      case 128:
+        if (stream) k_attn_few<128, true><<<grid, 512, 0, st>>>(a);
+        else k_attn_few<128, false><<<grid, 512, 0, st>>>(a);
+        break;
+      default: return hipErrorInvalidValue;
+    }
+  } else if (dtype == RV_BF16) {
     const unsigned units = (unsigned)(a.nsplit * groups);
     const dim3 grid((units + 7) / 8 * 8 * n_qgroups);
     if (qpw != 128 && qpw != 192) return hipErrorInvalidValue;

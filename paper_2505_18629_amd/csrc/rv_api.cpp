@@ -332,11 +332,13 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
   const int G = mc.n_heads / mc.n_kv_heads;
   const int qmax = G * max_seg_rows;
   const int groups = nseg * mc.n_kv_heads;
-  const int qpw = plan_attn_queries(dt == RV_BF16, qmax);
+  const bool few = dt == RV_BF16 && qmax <= kFewQueries;
+  const int qpw = few ? kFewQueries : plan_attn_queries(dt == RV_BF16, qmax);
   const int qgroups = (qmax + qpw - 1) / qpw;
   // Key split (plan_attn_split; 70B batch 8 at 8K context: 4 splits, 768
   // workgroups, 348 us per layer vs 393 us with 3 splits and 576).
-  const int ks = plan_attn_split(kmax, nseg, h_seg_end, h_seg_rows, mc.n_kv_heads, G, qmax, c->part_entries, qpw);
+  const int ks = few ? plan_attn_few_split(kmax, nseg, h_seg_end, mc.n_kv_heads, 8 * hd, qmax, c->part_entries)
+                     : plan_attn_split(kmax, nseg, h_seg_end, h_seg_rows, mc.n_kv_heads, G, qmax, c->part_entries, qpw);
   if (ks == 0) return rv_fail(RV_E_CAPACITY, "attention partial buffer too small for %d keys", kmax);
   const int nsplit = (kmax + ks - 1) / ks;
 
@@ -434,7 +436,7 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
       Prof pf(c, RV_PROF_ATTN, st);
       HIP_TRY(launch_attention(dt, at, qgroups, qpw, st), "attention");
     }
-    {
+    if (!(few && nsplit == 1)) {
       Prof pf(c, RV_PROF_COMBINE, st);
       HIP_TRY(launch_attn_combine(dt, at, st), "attention combine");
     }

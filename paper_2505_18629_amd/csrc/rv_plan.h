@@ -100,6 +100,37 @@ inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* se
   return ks;
 }
 
+// At most this many queries per (segment, kv head): k_attn_few, whose waves
+// share the queries and split the keys (bf16).
+constexpr int kFewQueries = 16;
+
+// Key split of one k_attn_few launch (a multiple of 64 keys; one split: no
+// combine kernel), or 0 if none fits.  Estimated us: 2.5 of launch and latency,
+// the keys of a workgroup at what one CU draws (kv_bytes per key), all keys
+// at what HBM gives, and for several splits the combine kernel.
+inline int plan_attn_few_split(int kmax, int nseg, const int* seg_end, int n_kv, int kv_bytes, int qmax,
+                               size_t part_entries) {
+  const int groups = nseg * n_kv;
+  long long keys = 0;
+  for (int s = 0; s < nseg; ++s) keys += seg_end[s];
+  const double stream = (double)keys * n_kv * kv_bytes / 5.5e6;
+  int ks = 0;
+  double best = 0;
+  for (int cand = 64; cand <= plan_round_up(kmax, 64); cand += 64) {
+    const int ns = (kmax + cand - 1) / cand;
+    if (ns > kMaxKeySplits || (size_t)ns * groups * qmax > part_entries) continue;
+    long long wgs = 0;
+    for (int s = 0; s < nseg; ++s) wgs += (long long)((seg_end[s] + cand - 1) / cand) * n_kv;
+    const double cu = (double)((wgs + 255) / 256) * std::min(cand, kmax) * kv_bytes / 4.5e4;
+    const double t = 2.5 + std::max(cu, stream) + (ns > 1 ? 3.5 + 0.05 * ns : 0.0);
+    if (ks == 0 || t < best) {
+      best = t;
+      ks = cand;
+    }
+  }
+  return ks;
+}
+
 // Launch shape of a matmul on the wide kernel (k_wide.h): 256 or 128 output
 // rows x mt token tiles per workgroup, n_tg token groups, gk k-groups.
 struct WidePlan {
