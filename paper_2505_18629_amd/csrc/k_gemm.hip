@@ -325,8 +325,7 @@ hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_gemm_wide(int epi, const GemmArgs& a, bool rows256, int mt, hipStream_t st) {
-  const int kw = rows256 ? 1 : 2;
-  if (a.gk < 1 || (a.K / 32) % (a.gk * kw) || a.N % (rows256 ? 256 : 128) || (long long)a.n_tg * mt * 16 < a.M)
+  if (a.gk < 1 || (a.K / 32) % (2 * a.gk) || a.N % (rows256 ? 256 : 128) || (long long)a.n_tg * mt * 16 < a.M)
     return hipErrorInvalidValue;
   if (a.gk > 1 && epi != EPI_PARTIAL) return hipErrorInvalidValue;
   switch (epi) {

@@ -11,7 +11,9 @@
 // operands and weights would hold the weight stream to the operand ring's
 // depth; with the roles apart each keeps its own.
 //
-// Step s covers k-steps s*KW .. s*KW + KW-1 of the k-group.  Barrier s: the
+// Step s covers the k-steps 2s and 2s+1 of the k-group (with KW = 1 every
+// consumer takes both: against one k-step per barrier 1 - 5% at 172 - 2047
+// rows, 8B O at 2047 102.8 -> 97.2 us).  Barrier s: the
 // operands of steps s and s+1 are in LDS, and the buffer of step s-1 is free.
 // Having step s+1 early lets a consumer read the first operand chunk of the
 // next step before the barrier that ends this one; chunk i+1 is always read
@@ -55,7 +57,8 @@ struct WideCfg {
   static constexpr int DEPTH = 4;                        // weight ring, k-steps of a wave
   static constexpr int CH = NT * MT >= 32 || MT == 9 ? 2 : 4;      // operand tiles per LDS read chunk (registers)
   static constexpr int NCH = (2 * MT + CH - 1) / CH;
-  static constexpr int UNITS = KW * MT * 2;              // operand tiles of a step
+  static constexpr int KPB = 2 / KW;                     // k-steps of a wave per step
+  static constexpr int UNITS = 2 * MT * 2;               // operand tiles of a step (two k-steps, two planes)
   static constexpr int U = (UNITS + PW - 1) / PW;        // copies per producer wave and step
   static constexpr int NB = cmin(6, kWideLdsUnits / UNITS);  // LDS buffers
   static constexpr int RED = KW > 1 ? RW * NT * MT : 0;  // tiles exchanged by the k-halves
@@ -68,7 +71,7 @@ struct WideCfg {
 template <int NT, int MT, int RW, int KW, bool STREAM, int EPI>
 __global__ __launch_bounds__((WideCfg<NT, MT, RW, KW>::THREADS)) void k_gemm_wide(GemmArgs a, int items) {
   using C = WideCfg<NT, MT, RW, KW>;
-  constexpr int DEPTH = C::DEPTH, CH = C::CH, NCH = C::NCH, UNITS = C::UNITS, NB = C::NB;
+  constexpr int DEPTH = C::DEPTH, CH = C::CH, NCH = C::NCH, KPB = C::KPB, UNITS = C::UNITS, NB = C::NB;
   __shared__ u32x4 xs[C::LDS];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -79,7 +82,7 @@ __global__ __launch_bounds__((WideCfg<NT, MT, RW, KW>::THREADS)) void k_gemm_wid
   if (item >= items) return;
   const int tg = item % a.n_tg, rk = item / a.n_tg;
   const int rg = rk / a.gk, kg = rk % a.gk;
-  const int kb = kg * (ksteps / a.gk), ss = ksteps / (a.gk * KW);  // first k-step, steps
+  const int kb = kg * (ksteps / a.gk), ss = ksteps / (a.gk * 2);  // first k-step, steps
 
   if (w >= RW * KW) {
     // ---- producer
@@ -98,7 +101,7 @@ __global__ __launch_bounds__((WideCfg<NT, MT, RW, KW>::THREADS)) void k_gemm_wid
       s = min(s, ss - 1);  // past the end: a valid step, not read
 #pragma unroll
       for (int u = 0; u < C::U; ++u)
-        __builtin_amdgcn_global_load_lds((const void*)(src[u] + (size_t)s * KW * 64),
+        __builtin_amdgcn_global_load_lds((const void*)(src[u] + (size_t)s * 128),
                                          (__attribute__((address_space(3))) void*)(&xs[buf * UNITS * 64 + dst[u]]), 16,
                                          0, 0);
     };
@@ -127,21 +130,23 @@ __global__ __launch_bounds__((WideCfg<NT, MT, RW, KW>::THREADS)) void k_gemm_wid
     for (int m = 0; m < MT; ++m) acc[n][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   u32x4 wq[DEPTH][NT];
-  auto load = [&](int slot, int s) {
-    s = min(s, ss - 1);
+  // the j-th k-step of this wave is kb + kw + j KW
+  auto load = [&](int slot, int j) {
+    j = min(j, ss * KPB - 1);
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      const u32x4* p = wp + ((size_t)n * ksteps + (size_t)s * KW) * 64;
+      const u32x4* p = wp + ((size_t)n * ksteps + (size_t)j * KW) * 64;
       wq[slot][n] = STREAM ? __builtin_nontemporal_load(p) : *p;
     }
   };
-  // operand tile t of a step: plane t / MT, token tile t % MT
+  // operand tile t of k-step sub of a step: plane t / MT, token tile t % MT
   bf16x8_t xr[2][CH];
   const u32x4* xbase = &xs[kw * MT * 2 * 64 + lane];
-  auto read = [&](int par, int i, int buf) {
+  auto read = [&](int par, int sub, int i, int buf) {
 #pragma unroll
     for (int c = 0; c < CH; ++c)
-      if (i * CH + c < 2 * MT) xr[par][c] = __builtin_bit_cast(bf16x8_t, xbase[(buf * UNITS + i * CH + c) * 64]);
+      if (i * CH + c < 2 * MT)
+        xr[par][c] = __builtin_bit_cast(bf16x8_t, xbase[(buf * UNITS + sub * 2 * MT + i * CH + c) * 64]);
   };
   auto multiply = [&](int par, int i, int slot) {
 #pragma unroll
@@ -157,31 +162,38 @@ __global__ __launch_bounds__((WideCfg<NT, MT, RW, KW>::THREADS)) void k_gemm_wid
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) load(d, d);
   int buf = 0, s = 0;
-  // One step from ring slot d; chunk 0 of its operands was read before.
+  // One step, the d-th of a turn of the ring; chunk 0 of its operands was read
+  // before.
   auto step = [&](int d, bool more) {
     const int next = buf == NB - 1 ? 0 : buf + 1;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int par = (d * NCH + i) & 1;
-      if (i + 1 < NCH) read(par ^ 1, i + 1, buf);
-      else read(par ^ 1, 0, next);  // after the last step: read and not used
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(par, i, d);
+    for (int sub = 0; sub < KPB; ++sub) {
+      const int slot = d * KPB + sub;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        const int par = (slot * NCH + i) & 1;
+        if (i + 1 < NCH) read(par ^ 1, sub, i + 1, buf);
+        else if (sub + 1 < KPB) read(par ^ 1, sub + 1, 0, buf);
+        else read(par ^ 1, 0, 0, next);  // after the last step: read and not used
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(par, i, slot);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (more) load(slot, (s + d) * KPB + sub + DEPTH);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (more) load(d, s + d + DEPTH);
-    __builtin_amdgcn_sched_barrier(0);
     buf = next;
     __syncthreads();  // barrier s + d + 1
   };
   __syncthreads();  // barrier 0
-  read(0, 0, 0);
-  for (; s + DEPTH <= ss; s += DEPTH) {
+  read(0, 0, 0, 0);
+  constexpr int TURN = DEPTH / KPB;
+  for (; s + TURN <= ss; s += TURN) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) step(d, true);
+    for (int d = 0; d < TURN; ++d) step(d, true);
   }
 #pragma unroll
-  for (int d = 0; d < DEPTH - 1; ++d)
+  for (int d = 0; d < TURN - 1; ++d)
     if (s + d < ss) step(d, false);
 
   // The two k-halves of a row tile add up: each gives the other half of its

@@ -60,8 +60,8 @@ struct GemmArgs {
 // mtt: token tiles (1, 2, 4; 1 or 2 with nt = 8).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int mtt, hipStream_t st);
 // bf16, 33 rows and more: 256 (rows256) or 128 output rows x mt (2 - 9) token tiles per
-// workgroup, n_tg = ceil(M / (16*mt)) token groups; N a multiple of the rows, K/32 of gk
-// (of 2*gk without rows256); gk > 1 only with EPI_PARTIAL.
+// workgroup, n_tg = ceil(M / (16*mt)) token groups; N a multiple of the rows, K/32 of
+// 2*gk; gk > 1 only with EPI_PARTIAL.
 hipError_t launch_gemm_wide(int epi, const GemmArgs& a, bool rows256, int mt, hipStream_t st);
 // its instantiations, one file each
 hipError_t launch_wide_store(const GemmArgs& a, bool rows256, int mt, hipStream_t st);

@@ -175,14 +175,14 @@ inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, 
   double best = 0;
   for (int r = 0; r < 2; ++r) {
     const bool r256 = r == 1;
-    const int rows = r256 ? 256 : 128, kw = r256 ? 1 : 2;
+    const int rows = r256 ? 256 : 128;
     if (N % rows) continue;
     for (int mt = 2; mt <= 9; ++mt) {
       // us per k-step of a workgroup: 16 row tiles on 4 waves, or 8 on 4 x 2
       const double step = r256 ? 0.2886 + 0.0334 * mt : 0.1133 + 0.0306 * mt;
       for (int gk : {1, 2, 3, 4, 6, 7, 8}) {
         if (gk > 1 && (!allow_split || gk * M > part_rows)) break;
-        if (ksteps % (gk * kw)) continue;
+        if (ksteps % (2 * gk)) continue;  // steps of two k-steps
         const double t = plan_matmul_us(step, rows, mt, M, N, K, gk, split_us);
         if (!p.use || t < best) {
           best = t;

@@ -23,9 +23,9 @@ int main() {
             const WidePlan p = plan_wide(M, m.N, m.K, split != 0, part_rows, us);
             if (!p.use) continue;
             ++planned;
-            const int rows = p.rows256 ? 256 : 128, kw = p.rows256 ? 1 : 2, ks = m.K / 32;
+            const int rows = p.rows256 ? 256 : 128, ks = m.K / 32;
             const bool ok = M >= kWideMinRows && m.N % rows == 0 && p.mt >= 2 && p.mt <= 9 && p.gk >= 1 &&
-                            ks % (p.gk * kw) == 0 && ks / (p.gk * kw) >= 1 && (p.gk == 1 || split) &&
+                            ks % (p.gk * 2) == 0 && ks / (p.gk * 2) >= 1 && (p.gk == 1 || split) &&
                             (p.gk == 1 || (long long)p.gk * M <= part_rows) && (long long)p.n_tg * p.mt * 16 >= M &&
                             (long long)(p.n_tg - 1) * p.mt * 16 < M &&
                             (long long)(m.N / rows) * p.gk * p.n_tg < (1LL << 30);
