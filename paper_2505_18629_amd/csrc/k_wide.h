@@ -6,7 +6,11 @@
 //    token tiles at the k-steps kw, kw + KW, ...; its weights go straight from
 //    global memory to a register ring DEPTH k-steps deep.
 //  - PW producer waves copy the operand tiles (hi and lo planes) of the next
-//    steps into a ring of NB LDS buffers with 16-byte direct loads.
+//    steps into a ring of NB LDS buffers with 16-byte direct loads.  Their
+//    barriers leave copies in flight (with __syncthreads every copy had to land
+//    before the next barrier: 14B gate/up at 172 rows 109 -> 98 us, 8B down at
+//    203 rows 53 -> 52, 70B gate/up at 360 rows 597 -> 548, with two k-steps per
+//    barrier).
 // Loads of one wave retire in issue order, so a wave that fetched both
 // operands and weights would hold the weight stream to the operand ring's
 // depth; with the roles apart each keeps its own.
@@ -46,9 +50,6 @@ constexpr int kWideLdsUnits = 160;  // 1 KiB operand tiles that fit the 160 KiB 
 
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-
-// s_waitcnt operand: vmcnt <= n, the other counters free.
-constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
 template <int NT, int MT, int RW, int KW>
 struct WideCfg {
@@ -109,7 +110,7 @@ __global__ __launch_bounds__((WideCfg<NT, MT, RW, KW>::THREADS)) void k_gemm_wid
     int buf = NB - 1;
     for (int s = 0; s < ss; ++s) {
       __builtin_amdgcn_s_waitcnt(wait_vm((NB - 3) * C::U));  // this wave's copies of steps <= s + 1 have landed
-      __syncthreads();                                       // barrier s
+      barrier_keep_loads();                                  // barrier s
       fetch(s + NB - 1, buf);                                // into the buffer of step s - 1
       buf = buf == NB - 1 ? 0 : buf + 1;
     }

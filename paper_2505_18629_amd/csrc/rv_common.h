@@ -183,6 +183,22 @@ RV_DEV __host__ inline size_t mat_packed_offset(const MatDesc& m, int p, int k, 
   return (((size_t)(p >> 4) * ksteps + tile_k) * 1024) + (size_t)lane * 16 + (size_t)j * es;
 }
 
+// s_waitcnt operand: at most n vector memory operations outstanding, the other
+// counters free.
+constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+
+// Workgroup barrier for waves with direct global -> LDS copies in flight: this
+// wave's LDS accesses are done, its loads are not waited for.  (The release
+// fence of __syncthreads waits for every outstanding copy, which would end
+// each copy's flight at the next barrier.)  Before data that a copy brings is
+// used, its wave waits for it (wait_vm) and then takes part in a barrier.
+RV_DEV void barrier_keep_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // ---------------------------------------------------------------- work items
 
 // Item of workgroup b in a launch of `items` rounded up to a multiple of 8
