@@ -436,7 +436,7 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
       Prof pf(c, RV_PROF_ATTN, st);
       HIP_TRY(launch_attention(dt, at, qgroups, qpw, st), "attention");
     }
-    if (!(few && nsplit == 1)) {
+    if (!(dt == RV_BF16 && nsplit == 1)) {  // one split: the output is final
       Prof pf(c, RV_PROF_COMBINE, st);
       HIP_TRY(launch_attn_combine(dt, at, st), "attention combine");
     }
