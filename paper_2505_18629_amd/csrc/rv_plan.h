@@ -67,18 +67,26 @@ inline bool next_prefill_chunk(const int* L, int B, int rows_cap, int& b, int& p
 }
 
 // Queries per workgroup of the bf16 attention kernel: 128 (8 waves of one
-// 16-query tile), or 192 (12 waves) when a kv head has 129-192 queries,
-// which would otherwise take a second, mostly idle group of 128 (5 query
-// heads per kv head x 31 block rows = 155, e.g. the 14B shape at k = 5 with a
-// 16-token probe: 4 x 2048 keys, 30.4-32.7 -> 27.5-29.0 us per launch).
-inline int plan_attn_queries(bool bf16, int qmax) { return bf16 && qmax > 128 && qmax <= 192 ? 192 : 128; }
+// 16-query tile), or 192 (12 waves) where groups of 192 cover a kv head's queries
+// with no more query slots.  A tile's copy then serves half as many queries
+// again and three waves per SIMD hide more latency: 129-192 queries take one
+// group instead of a second, mostly idle one of 128 (148 queries, the 8B shape
+// with up to 8 drafts: 44 -> 35 us per launch), 360 queries (70B, 45 rows) two
+// groups instead of three (320 -> 280).  With more slots it loses (215 queries,
+// 14B: 36 -> 43 us).
+inline int plan_attn_queries(bool bf16, int qmax) {
+  return bf16 && qmax > 128 && (qmax + 191) / 192 * 192 <= (qmax + 127) / 128 * 128 ? 192 : 128;
+}
 
 // Key split of one attention launch (a multiple of 64 keys), or 0 if none
 // fits.  Minimises the estimated time: rounds of 256 workgroups (one per CU)
 // x (64-key tiles per workgroup + a per-workgroup overhead of about two
-// tiles), counting the workgroups that have keys (segment s has keys
-// 0 .. seg_end[s]-1 and G * seg_rows[s] queries per kv head, in groups of
-// qpw); bounded by the partial buffer (splits x segments x kv heads x qmax
+// tiles) x 2.9 us per tile, counting the workgroups that have keys (segment s
+// has keys 0 .. seg_end[s]-1 and G * seg_rows[s] queries per kv head, in groups
+// of qpw), and for several splits the combine kernel (4 us, and 512 bytes per
+// partial and output row at 3.5 TB/s; a bf16 launch of one split needs none:
+// 2048-row prefill chunks otherwise split in two, 8B prefill 13.46 -> 13.94 ms);
+// bounded by the partial buffer (splits x segments x kv heads x qmax
 // entries) and by the combine kernel's kMaxKeySplits splits per query.
 inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* seg_rows, int n_kv, int G, int qmax,
                            size_t part_entries, int qpw = 128) {
@@ -91,7 +99,8 @@ inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* se
     long long wgs = 0;
     for (int s = 0; s < nseg; ++s)
       wgs += (long long)((seg_end[s] + cand - 1) / cand) * n_kv * ((G * seg_rows[s] + qpw - 1) / qpw);
-    const double t = (double)((wgs + 255) / 256) * (cand / 64 + 2);
+    const double combine = ns > 1 ? 4 + (double)(ns + 1) * groups * qmax * 512 / 3.5e6 : 0;
+    const double t = (double)((wgs + 255) / 256) * (cand / 64 + 2) * 2.9 + combine;
     if (ks == 0 || t < best) {
       best = t;
       ks = cand;
@@ -149,8 +158,9 @@ constexpr int kWideMinRows = 33;  // fewer rows: the few-row kernel
 // MFMA power (1.76 PFLOP/s of hi/lo products).  k-group partials are written
 // at 3.3 and read by the consumer at 5 TB/s.  Fitted to 5600 launches: 16
 // matrices (1B, 8B, 14B, 70B) and the LM heads at 20 - 2047 rows, every shape
-// and k-group count; error 9% rms, and the shape it picks costs 1.5% more
-// than the best one in the mean, 25% at worst (a 10 us launch).
+// and k-group count; error 9% rms.  Over 4200 launches of the present kernel,
+// operands freshly written before each, the shape it picks costs 1.0% more
+// than the best one in the mean, 19% at worst (a 10 us launch).
 inline double plan_matmul_us(double step, int rows, int mt, int M, int N, int K, int gk, double split_us) {
   const int n_tg = (M + 16 * mt - 1) / (16 * mt);
   const long long items = (long long)(N / rows) * gk * n_tg;
@@ -165,8 +175,7 @@ inline double plan_matmul_us(double step, int rows, int mt, int M, int N, int K,
 
 // bf16 matmuls of 33 rows and more: the cheapest of the wide kernel's shapes,
 // or use = false where the 512-row kernel costs less (hundreds of rows that
-// fill its 512 x 128 tiles: 8B gate/up at 496 tokens 184 against 195 us) or
-// no shape divides the matrix.  split_us: cost of splitting K beyond the
+// fill its 512 x 128 tiles) or no shape divides the matrix.  split_us: cost of splitting K beyond the
 // partials' traffic (the QKV projection then needs its finish kernel).
 inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, double split_us = 0) {
   WidePlan p{};
@@ -191,8 +200,9 @@ inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, 
       }
     }
   }
-  // the 512-row kernel where it fills its rounds: about 3% under two rounds of
-  // 256 rows (8B gate/up at 1024 tokens 373 against 383 us)
+  // the 512-row kernel where it fills its rounds: 1 - 4% under two rounds of
+  // 256 rows (8B gate/up at 1024 tokens 359 against 366 us, 70B at 2047 2555
+  // against 2660)
   if (p.use && N % 512 == 0 && ksteps % 4 == 0 && plan_matmul_us(1.07, 512, 8, M, N, K, 1, 0) < best) p.use = false;
   return p;
 }
