@@ -8,8 +8,8 @@
 // argument for unidirectional attention, Section 3.1), and the probe and
 // second copy see everything before them.
 //
-// Work split: one workgroup per (key split, query group of 128 -- or 192 when
-// a kv head has 129-192 queries -- segment x kv head).  The G = Hq/Hkv query
+// Work split: one workgroup per (key split, query group of 128 -- or 192 where
+// that takes no more query slots -- segment x kv head).  The G = Hq/Hkv query
 // heads of a kv head share each K/V tile, so a verify block of S rows gives
 // G*S queries per kv head (124 for the 8B shape).
 // Each split writes unnormalised partial results; a second kernel combines
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a, int hd) {
   const int grp = blockIdx.y;
   const int seg = grp / a.n_kv, kvh = grp % a.n_kv;
   const int G = a.n_heads / a.n_kv;
-  const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int q = xcd_row(blockIdx.x, (a.qmax + 3) / 4) * 4 + (threadIdx.x >> 6);
   const int nrows = a.seg_n[seg];
   if (q >= G * nrows) return;
   const int pos_q = a.seg_pos0[seg] + q / G;
@@ -764,7 +764,7 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, int n_qgroups, int qpw
 }
 
 hipError_t launch_attn_combine(int dtype, const AttnArgs& a, hipStream_t st) {
-  dim3 grid((a.qmax + 3) / 4, a.nseg * a.n_kv);
+  dim3 grid(xcd_grid((a.qmax + 3) / 4), a.nseg * a.n_kv);
   if (dtype == RV_BF16)
     k_attn_combine<RV_BF16><<<grid, 256, 0, st>>>(a, a.hd);
   else

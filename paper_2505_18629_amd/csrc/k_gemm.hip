@@ -1,6 +1,7 @@
 // Weight-streaming matrix kernel: Y[t][p] = sum_k X[t][k] W[p][k] for the
-// few-token activations of a verify block (M = batch * block rows) and, with
-// more token groups, for prefill chunks.
+// few-token activations of a verify block (M = batch * block rows): bf16 up to
+// 32 rows, fp32 with any number of them (more token groups); and the 512-row
+// kernel for hundreds of bf16 rows.
 //
 // Layout and schedule
 //  - W is packed in 1 KiB tiles of 16 rows x KT k; activations are stored in

@@ -23,8 +23,9 @@ template <int DT, int NPT, int PB>
 __global__ __launch_bounds__(1024) void k_rmsnorm(float* __restrict__ h, int d, const float* __restrict__ gain,
                                                   float eps, void* __restrict__ out, void* __restrict__ out2,
                                                   const int* __restrict__ gather, const float* __restrict__ P,
-                                                  int pk, int prows) {
-  const int r = blockIdx.x;
+                                                  int pk, int prows, int rows) {
+  const int r = xcd_row(blockIdx.x, rows);
+  if (r >= rows) return;
   const int src = gather ? gather[r] : r;
   float* x = h + (size_t)src * d;
   f32x4_t v[NPT], gg[NPT];
@@ -153,7 +154,8 @@ RV_DEV void qkv_finish_unit(const QkvFinish& a, int tok, int tile, int r0) {
 // of a 16-row tile and their rotary partners r0+8..r0+11 (r0 in {0, 4}).
 template <int DT, int PB>
 __global__ __launch_bounds__(256) void k_qkv_finish(QkvFinish a) {
-  const int tok = blockIdx.x;
+  const int tok = xcd_row(blockIdx.x, a.M);
+  if (tok >= a.M) return;
   const int units = a.N / 8;
   for (int u = blockIdx.y * blockDim.x + threadIdx.x; u < units; u += gridDim.y * blockDim.x)
     qkv_finish_unit<DT, PB>(a, tok, u >> 1, (u & 1) * 4);
@@ -287,7 +289,7 @@ hipError_t launch_rmsnorm(int dtype, float* h, int rows, int d, const float* gai
   if (threads > 1024 || threads % 64) return hipErrorInvalidValue;
   const int pb = pk <= 2 ? 2 : pk <= 4 ? 4 : 8;
 #define RV_NORM(DT_, N_, PB_) \
-  k_rmsnorm<DT_, N_, PB_><<<rows, threads, 0, st>>>(h, d, gain, eps, out, out2, gather, P, pk, prows)
+  k_rmsnorm<DT_, N_, PB_><<<xcd_grid(rows), threads, 0, st>>>(h, d, gain, eps, out, out2, gather, P, pk, prows, rows)
 #define RV_NORM_PB(DT_, N_)       \
   if (pb == 2) RV_NORM(DT_, N_, 2); \
   else if (pb == 4) RV_NORM(DT_, N_, 4); \
@@ -306,7 +308,7 @@ hipError_t launch_qkv_finish(int dtype, const QkvFinish& a, hipStream_t st) {
   // workgroups of 256 threads, one unit each, spread over as many
   // workgroups per token as the units need (8B: 768 units, 3 per token)
   const int units = a.N / 8;
-  const dim3 grid(a.M, (units + 255) / 256);
+  const dim3 grid(xcd_grid(a.M), (units + 255) / 256);
   const int pb = a.gk <= 2 ? 2 : a.gk <= 4 ? 4 : 8;
 #define RV_FIN(DT_, PB_) k_qkv_finish<DT_, PB_><<<grid, 256, 0, st>>>(a)
   if (dtype == RV_BF16) {

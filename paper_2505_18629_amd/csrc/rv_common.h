@@ -211,6 +211,19 @@ RV_DEV int xcd_item(int b, int items) {
   return b % 8 * per + b / 8;
 }
 
+// Row of workgroup b of a kernel with a workgroup per row (or few queries) that
+// writes operand tiles or the cache.  A row's share of a tile is 16 bytes (of the
+// V cache 2) every 256, so a 128-byte line holds 8 rows and more: with
+// neighbouring rows on eight XCDs each line is written in pieces by eight L2s,
+// with runs of rows behind one L2 it leaves whole (RMSNorm of 2048 x 4096 32.3 ->
+// 17.9 us, 716 x 2048 7.3 -> 5.6; 8B batch-1 pass, 31 rows, 3953 -> 3904, its
+// norms, finish and combine together).  Under kXcdRows rows the plain order: the
+// line is short anyway and the empty workgroups cost (1B decode steps of 1 and
+// 16 rows, combine launches of one workgroup per head: 858 -> 868, 1175 -> 1190).
+constexpr int kXcdRows = 24;
+RV_DEV int xcd_row(int b, int rows) { return rows < kXcdRows ? b : xcd_item(b, rows); }
+inline unsigned xcd_grid(int rows) { return (unsigned)(rows < kXcdRows ? rows : (rows + 7) / 8 * 8); }
+
 // ---------------------------------------------------------------- reductions
 
 // Reductions over the four lanes that share l % 16 (l, l^16, l^32, l^48) with

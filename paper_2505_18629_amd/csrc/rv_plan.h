@@ -1,6 +1,7 @@
 // Host-side planning of a pass: workspace row capacities, prefill chunks,
-// matmul launch shapes and the attention key split.  Plain integer arithmetic with no HIP types, so
-// the same code also builds for the CPU alone (the host checks under tests/).
+// matmul launch shapes and the attention key split.  Plain arithmetic with no
+// HIP types, so the same code also builds for the CPU alone (the host checks
+// under tests/).
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -175,8 +176,9 @@ inline double plan_matmul_us(double step, int rows, int mt, int M, int N, int K,
 
 // bf16 matmuls of 33 rows and more: the cheapest of the wide kernel's shapes,
 // or use = false where the 512-row kernel costs less (hundreds of rows that
-// fill its 512 x 128 tiles) or no shape divides the matrix.  split_us: cost of splitting K beyond the
-// partials' traffic (the QKV projection then needs its finish kernel).
+// fill its 512 x 128 tiles) or no shape divides the matrix.  split_us: cost of
+// splitting K beyond the partials' traffic (the QKV projection then needs its
+// finish kernel).
 inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, double split_us = 0) {
   WidePlan p{};
   if (M < kWideMinRows || N % 128) return p;
