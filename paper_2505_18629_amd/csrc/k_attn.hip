@@ -14,9 +14,9 @@
 // G*S queries per kv head (124 for the 8B shape).
 // Each split writes unnormalised partial results; a second kernel combines
 // splits in a fixed order (deterministic).  With one split (prefill chunks, whose
-// query groups fill the chip) the bf16 kernels write the output themselves: the
-// combine launch took 42 of 369 us per layer of a 2048-row 8B prefill chunk,
-// 15 of 28 us at 716 rows of the 1B shape.
+// query groups fill the chip, or whose partials would not fit) the kernels write
+// the output themselves: the combine launch took 42 of 369 us per layer of a
+// 2048-row 8B prefill chunk, 15 of 28 us at 716 rows of the 1B shape.
 #include "rv_internal.h"
 
 namespace {
@@ -587,7 +587,18 @@ __global__ __launch_bounds__(512) void k_attn_f32(AttnArgs a) {
       }
   }
   if (q >= Q) return;
-  // lane holds dims (4g + i) DC + t of query q
+  // lane holds dims (4g + i) DC + t of query q: a run of 4 DC
+  if (a.nsplit == 1) {
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int u = 0; u < DC; ++u) {
+      f32x4_t x;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = o[(4 * u + j) % DC][(4 * u + j) / DC] * inv;
+      put_operand4<RV_F32>(a.out, a.out2, qrow, qcol + 4 * g * DC + 4 * u, a.n_heads * HD, x);
+    }
+    return;
+  }
   const size_t e = ((size_t)split * (a.nseg * a.n_kv) + grp) * a.qmax + q;
 #pragma unroll
   for (int i = 0; i < 4; ++i)

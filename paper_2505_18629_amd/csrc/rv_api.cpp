@@ -339,7 +339,6 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
   // workgroups, 348 us per layer vs 393 us with 3 splits and 576).
   const int ks = few ? plan_attn_few_split(kmax, nseg, h_seg_end, mc.n_kv_heads, 8 * hd, qmax, c->part_entries)
                      : plan_attn_split(kmax, nseg, h_seg_end, h_seg_rows, mc.n_kv_heads, G, qmax, c->part_entries, qpw);
-  if (ks == 0) return rv_fail(RV_E_CAPACITY, "attention partial buffer too small for %d keys", kmax);
   const int nsplit = (kmax + ks - 1) / ks;
 
   AttnArgs at{};
@@ -436,7 +435,7 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
       Prof pf(c, RV_PROF_ATTN, st);
       HIP_TRY(launch_attention(dt, at, qgroups, qpw, st), "attention");
     }
-    if (!(dt == RV_BF16 && nsplit == 1)) {  // one split: the output is final
+    if (nsplit > 1) {  // one split: the output is final
       Prof pf(c, RV_PROF_COMBINE, st);
       HIP_TRY(launch_attn_combine(dt, at, st), "attention combine");
     }

@@ -101,7 +101,7 @@ struct AttnArgs {
   float scale_log2;     // log2(e) / sqrt(hd)
 };
 // qpw: queries per workgroup (plan_attn_queries; 16 and 192 for bf16 only), n_qgroups = ceil(qmax / qpw).
-// bf16 and one split: the output is final (no combine).
+// One split: the output is final (no combine, no partials).
 hipError_t launch_attention(int dtype, const AttnArgs& a, int n_qgroups, int qpw, hipStream_t st);
 hipError_t launch_attn_combine(int dtype, const AttnArgs& a, hipStream_t st);
 // Copies positions pos0 .. pos0+npos-1 of every kv head of one sequence out of

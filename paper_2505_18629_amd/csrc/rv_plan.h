@@ -79,16 +79,21 @@ inline int plan_attn_queries(bool bf16, int qmax) {
   return bf16 && qmax > 128 && (qmax + 191) / 192 * 192 <= (qmax + 127) / 128 * 128 ? 192 : 128;
 }
 
-// Key split of one attention launch (a multiple of 64 keys), or 0 if none
-// fits.  Minimises the estimated time: rounds of 256 workgroups (one per CU)
+inline bool plan_split_fits(int ns, int groups, int qmax, size_t part_entries) {
+  return ns == 1 || (ns <= kMaxKeySplits && (size_t)ns * groups * qmax <= part_entries);
+}
+
+// Key split of one attention launch (a multiple of 64 keys).  Minimises the estimated time: rounds of 256 workgroups (one per CU)
 // x (64-key tiles per workgroup + a per-workgroup overhead of about two
 // tiles) x 2.9 us per tile, counting the workgroups that have keys (segment s
 // has keys 0 .. seg_end[s]-1 and G * seg_rows[s] queries per kv head, in groups
 // of qpw), and for several splits the combine kernel (4 us, and 512 bytes per
-// partial and output row at 3.5 TB/s; a bf16 launch of one split needs none:
-// 2048-row prefill chunks otherwise split in two, 8B prefill 13.46 -> 13.94 ms);
-// bounded by the partial buffer (splits x segments x kv heads x qmax
-// entries) and by the combine kernel's kMaxKeySplits splits per query.
+// partial and output row at 3.5 TB/s; one split needs none: 2048-row prefill
+// chunks otherwise split in two, 8B prefill 13.46 -> 13.94 ms).  Several splits
+// are bounded by the partial buffer (splits x segments x kv heads x qmax
+// entries) and by the combine kernel's kMaxKeySplits splits per query; one split
+// writes no partials and so always fits (a chunk of one long and many short
+// prefixes can have more entries than the buffer, which follows its rows).
 inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* seg_rows, int n_kv, int G, int qmax,
                            size_t part_entries, int qpw = 128) {
   const int groups = nseg * n_kv;
@@ -96,7 +101,7 @@ inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* se
   double best = 0;
   for (int cand = 64; cand <= plan_round_up(kmax, 64); cand += 64) {
     const int ns = (kmax + cand - 1) / cand;
-    if (ns > kMaxKeySplits || (size_t)ns * groups * qmax > part_entries) continue;
+    if (!plan_split_fits(ns, groups, qmax, part_entries)) continue;
     long long wgs = 0;
     for (int s = 0; s < nseg; ++s)
       wgs += (long long)((seg_end[s] + cand - 1) / cand) * n_kv * ((G * seg_rows[s] + qpw - 1) / qpw);
@@ -115,7 +120,7 @@ inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* se
 constexpr int kFewQueries = 16;
 
 // Key split of one k_attn_few launch (a multiple of 64 keys; one split: no
-// combine kernel), or 0 if none fits.  Estimated us: 2.5 of launch and latency,
+// combine kernel; bounds as above).  Estimated us: 2.5 of launch and latency,
 // the keys of a workgroup at what one CU draws (kv_bytes per key), all keys
 // at what HBM gives, and for several splits the combine kernel.
 inline int plan_attn_few_split(int kmax, int nseg, const int* seg_end, int n_kv, int kv_bytes, int qmax,
@@ -128,7 +133,7 @@ inline int plan_attn_few_split(int kmax, int nseg, const int* seg_end, int n_kv,
   double best = 0;
   for (int cand = 64; cand <= plan_round_up(kmax, 64); cand += 64) {
     const int ns = (kmax + cand - 1) / cand;
-    if (ns > kMaxKeySplits || (size_t)ns * groups * qmax > part_entries) continue;
+    if (!plan_split_fits(ns, groups, qmax, part_entries)) continue;
     long long wgs = 0;
     for (int s = 0; s < nseg; ++s) wgs += (long long)((seg_end[s] + cand - 1) / cand) * n_kv;
     const double cu = (double)((wgs + 255) / 256) * std::min(cand, kmax) * kv_bytes / 4.5e4;
