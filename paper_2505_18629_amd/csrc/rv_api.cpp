@@ -223,7 +223,7 @@ size_t cache_layout(rv_cache* c, void* buf) {
   c->lm_x2 = cv.take<void*>((size_t)c->out_rows_cap * d * e2);
   c->part_o = cv.take<float*>(c->part_entries * hd * 4);
   c->part_ml = cv.take<float*>(c->part_entries * 2 * 4);
-  c->gpart_rows = std::max(kMaxSplitK * kSplitRows, kMaxSplitTiled * round_up(c->B * c->max_block, 64));
+  c->gpart_rows = cache_part_rows(c->B, c->max_block);
   c->gpart = cv.take<float*>((size_t)c->gpart_rows * std::max(d, c->m->qkv.N) * 4);
   c->logits = cv.take<float*>((size_t)c->out_rows_cap * mc.vocab * 4);
   c->z = cv.take<float*>((size_t)c->r1_cap * mc.vocab * 4);
@@ -290,21 +290,9 @@ struct Prof {
   }
 };
 
-constexpr double kQkvSplitUs = 4.0;  // a split QKV projection's finish kernel, beside its traffic
-
-// Launch shape of one matmul of this model: plan_wide's, else plan_matmul's.
-struct MatPlan {
-  WidePlan wide;
-  GemmPlan gemm;
-  int gk() const { return wide.use ? wide.gk : gemm.gk; }
-};
-
-MatPlan plan_mat(const rv_cache* c, int epi, int M, int N, int K, bool allow_split, double split_us = 0) {
-  const bool bf16 = c->m->cfg.dtype == RV_BF16;
-  MatPlan p{};
-  if (bf16) p.wide = plan_wide(M, N, K, allow_split, c->gpart_rows, split_us);
-  if (!p.wide.use) p.gemm = plan_matmul(bf16, epi == EPI_SWIGLU, M, N, K, allow_split, c->gpart_rows);
-  return p;
+// Launch shape of one matmul of this model.
+MatPlan plan_for(const rv_cache* c, int epi, int M, int N, int K, bool allow_split) {
+  return plan_mat(c->m->cfg.dtype == RV_BF16, epi == EPI_SWIGLU, M, N, K, allow_split, c->gpart_rows);
 }
 
 // EPI_RESID of a split plan writes its k-group partials (EPI_PARTIAL).
@@ -331,15 +319,8 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
   const int dt = mc.dtype, d = mc.d_model, hd = mc.head_dim;
   const int G = mc.n_heads / mc.n_kv_heads;
   const int qmax = G * max_seg_rows;
-  const int groups = nseg * mc.n_kv_heads;
-  const bool few = dt == RV_BF16 && qmax <= kFewQueries;
-  const int qpw = few ? kFewQueries : plan_attn_queries(dt == RV_BF16, qmax);
-  const int qgroups = (qmax + qpw - 1) / qpw;
-  // Key split (plan_attn_split; 70B batch 8 at 8K context: 4 splits, 768
-  // workgroups, 348 us per layer vs 393 us with 3 splits and 576).
-  const int ks = few ? plan_attn_few_split(kmax, nseg, h_seg_end, mc.n_kv_heads, 8 * hd, qmax, c->part_entries)
-                     : plan_attn_split(kmax, nseg, h_seg_end, h_seg_rows, mc.n_kv_heads, G, qmax, c->part_entries, qpw);
-  const int nsplit = (kmax + ks - 1) / ks;
+  const AttnPlan ap = plan_attention(dt == RV_BF16, kmax, nseg, h_seg_end, h_seg_rows, max_seg_rows, mc.n_kv_heads, G,
+                                     hd, c->part_entries);
 
   AttnArgs at{};
   at.q = c->qbuf;
@@ -353,8 +334,8 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
   at.n_kv = mc.n_kv_heads;
   at.hd = hd;
   at.kv_len = c->kv_len;
-  at.ks = ks;
-  at.nsplit = nsplit;
+  at.ks = ap.ks;
+  at.nsplit = ap.nsplit;
   at.qmax = qmax;
   at.part_o = c->part_o;
   at.part_ml = c->part_ml;
@@ -364,12 +345,11 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
 
   // the same launch shapes in every layer
   const int qd = mc.n_heads * hd;
-  const MatPlan p_qkv = plan_mat(c, EPI_RESID, M, m->qkv.N, d, true, kQkvSplitUs);
-  const MatPlan p_qkv1 = p_qkv.gk() > 1 ? p_qkv : plan_mat(c, EPI_QKV, M, m->qkv.N, d, false);
-  const MatPlan p_o = plan_mat(c, EPI_RESID, M, d, qd, true);
-  const MatPlan p_gateup = plan_mat(c, EPI_SWIGLU, M, m->gateup.N, d, false);
-  const MatPlan p_down = plan_mat(c, EPI_RESID, M, d, mc.ffn_dim, true);
-  const MatPlan p_last = split_last ? p_down : plan_mat(c, EPI_RESID, M, d, mc.ffn_dim, false);
+  const MatPlan p_qkv = plan_qkv(dt == RV_BF16, M, m->qkv.N, d, c->gpart_rows);
+  const MatPlan p_o = plan_for(c, EPI_RESID, M, d, qd, true);
+  const MatPlan p_gateup = plan_for(c, EPI_SWIGLU, M, m->gateup.N, d, false);
+  const MatPlan p_down = plan_for(c, EPI_RESID, M, d, mc.ffn_dim, true);
+  const MatPlan p_last = split_last ? p_down : plan_for(c, EPI_RESID, M, d, mc.ffn_dim, false);
 
   int pending = 0;  // k-groups of the last residual matmul still in c->gpart
   for (int l = 0; l < mc.n_layers; ++l) {
@@ -423,7 +403,7 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
                      c->row_pos, c->row_seq, c->rope_cos, c->rope_sin, c->qbuf, c->qbuf2, kc, vc, kc2, vc2};
         HIP_TRY(launch_qkv_finish(dt, qf, st), "qkv finish");
       } else {
-        HIP_TRY(run_gemm(c, EPI_QKV, g, p_qkv1, st), "qkv");
+        HIP_TRY(run_gemm(c, EPI_QKV, g, p_qkv, st), "qkv");
       }
     }
 
@@ -433,9 +413,9 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
     at.vc2 = vc2;
     {
       Prof pf(c, RV_PROF_ATTN, st);
-      HIP_TRY(launch_attention(dt, at, qgroups, qpw, st), "attention");
+      HIP_TRY(launch_attention(dt, at, ap.n_qgroups, ap.qpw, st), "attention");
     }
-    if (nsplit > 1) {  // one split: the output is final
+    if (ap.nsplit > 1) {  // one split: the output is final
       Prof pf(c, RV_PROF_COMBINE, st);
       HIP_TRY(launch_attn_combine(dt, at, st), "attention combine");
     }
@@ -879,7 +859,7 @@ rv_status verify_impl(rv_cache* c, const int32_t* h_prefix_len, const int32_t* d
   gl.ldy = mc.vocab;
   {
     Prof pf(c, RV_PROF_LMHEAD, st);
-    HIP_TRY(run_gemm(c, EPI_STORE, gl, plan_mat(c, EPI_STORE, gl.M, gl.N, gl.K, false), st), "lm head");
+    HIP_TRY(run_gemm(c, EPI_STORE, gl, plan_for(c, EPI_STORE, gl.M, gl.N, gl.K, false), st), "lm head");
   }
 
   HeadArgs ha = head_args(c, k, kb, R1, n_probe, P, *fusion, d_q, seed, d_draft_ids, h_prefix_len, d_accept_len,
@@ -1155,19 +1135,19 @@ rv_status rv_debug_time_matrix(rv_cache* c, int32_t matrix, int32_t M, int32_t r
       case RV_MAT_O:
         g.W = m->w_o[l]; g.X = c->att; g.X2 = c->att2; g.N = d; g.K = mc.n_heads * mc.head_dim;
         g.Y = c->h; g.ldy = d; g.P = c->gpart;
-        return run_gemm(c, EPI_RESID, g, plan_mat(c, EPI_RESID, g.M, g.N, g.K, true), st);
+        return run_gemm(c, EPI_RESID, g, plan_for(c, EPI_RESID, g.M, g.N, g.K, true), st);
       case RV_MAT_GATEUP:
         g.W = m->w_gateup[l]; g.X = c->xn; g.X2 = c->xn2; g.N = m->gateup.N; g.K = d;
         g.act = c->act; g.act2 = c->act2;
-        return run_gemm(c, EPI_SWIGLU, g, plan_mat(c, EPI_SWIGLU, g.M, g.N, g.K, false), st);
+        return run_gemm(c, EPI_SWIGLU, g, plan_for(c, EPI_SWIGLU, g.M, g.N, g.K, false), st);
       case RV_MAT_DOWN:
         g.W = m->w_down[l]; g.X = c->act; g.X2 = c->act2; g.N = d; g.K = mc.ffn_dim;
         g.Y = c->h; g.ldy = d; g.P = c->gpart;
-        return run_gemm(c, EPI_RESID, g, plan_mat(c, EPI_RESID, g.M, g.N, g.K, true), st);
+        return run_gemm(c, EPI_RESID, g, plan_for(c, EPI_RESID, g.M, g.N, g.K, true), st);
       default:
         g.W = m->lm_head; g.X = c->lm_x; g.X2 = c->lm_x2; g.N = mc.vocab; g.K = d;
         g.Y = c->logits; g.ldy = mc.vocab;
-        return run_gemm(c, EPI_STORE, g, plan_mat(c, EPI_STORE, g.M, g.N, g.K, false), st);
+        return run_gemm(c, EPI_STORE, g, plan_for(c, EPI_STORE, g.M, g.N, g.K, false), st);
     }
   };
   if (matrix == RV_MAT_LM_HEAD && M > c->out_rows_cap) return rv_fail(RV_E_ARG, "M exceeds the LM-head rows");
@@ -1218,7 +1198,7 @@ rv_status rv_debug_linear(const rv_cache* c, int32_t layer, int32_t matrix, cons
   g.Y = d_y;
   g.ldy = md->N;
   g.md = *md;
-  HIP_TRY(run_gemm(c, EPI_STORE_LOGICAL, g, plan_mat(c, EPI_STORE_LOGICAL, g.M, g.N, g.K, false), st), "linear");
+  HIP_TRY(run_gemm(c, EPI_STORE_LOGICAL, g, plan_for(c, EPI_STORE_LOGICAL, g.M, g.N, g.K, false), st), "linear");
   return RV_OK;
 }
 

@@ -11,8 +11,8 @@ enum { RV_MAX_SEGS = 128 };   // query segments of one prefill chunk
 
 constexpr int kPrefillRows = 2048;    // rows per prefill chunk
 constexpr int kMaxSplitK = 16;        // k-groups of a split matmul
-constexpr int kMaxSplitTiled = 4;     // k-groups of a split matmul of a whole verify block that the partial buffer holds
-constexpr int kSplitRows = 64;        // matmuls with at most this many rows may split K
+constexpr int kPartBlocks = 4;        // k-groups of a whole verify block's rows that the partial buffer holds
+constexpr int kSplitRows = 64;        // the few-row kernel splits K for at most this many rows
 constexpr int kSplitsPerQuery = 8;    // attention partial-buffer depth per query row
 constexpr int kMaxKeySplits = 64;     // key splits the combine kernel merges per query
 
@@ -26,6 +26,11 @@ inline int cache_rows_cap(int batch, int max_block) {
 // Entries (query rows x heads x splits) of the attention partial buffers.
 inline size_t cache_part_entries(int rows_cap, int n_heads) {
   return (size_t)rows_cap * n_heads * kSplitsPerQuery;
+}
+
+// Rows of the matmuls' partial buffer: k-groups x rows of a split launch stay within it.
+inline int cache_part_rows(int batch, int max_block) {
+  return std::max(kMaxSplitK * kSplitRows, kPartBlocks * plan_round_up(batch * max_block, 64));
 }
 
 // One prefill chunk: up to rows_cap rows over (sequence, position < L - 1),
@@ -85,7 +90,8 @@ inline bool plan_split_fits(int ns, int groups, int qmax, size_t part_entries) {
 
 // Key split of one attention launch (a multiple of 64 keys).  Minimises the estimated time: rounds of 256 workgroups (one per CU)
 // x (64-key tiles per workgroup + a per-workgroup overhead of about two
-// tiles) x 2.9 us per tile, counting the workgroups that have keys (segment s
+// tiles; 70B batch 8 with 8K keys: 4 splits, 768 workgroups, 348 us when this was
+// chosen, 393 with 3 splits and 576) x 2.9 us per tile, counting the workgroups that have keys (segment s
 // has keys 0 .. seg_end[s]-1 and G * seg_rows[s] queries per kv head, in groups
 // of qpw), and for several splits the combine kernel (4 us, and 512 bytes per
 // partial and output row at 3.5 TB/s; one split needs none: 2048-row prefill
@@ -146,6 +152,28 @@ inline int plan_attn_few_split(int kmax, int nseg, const int* seg_end, int n_kv,
   return ks;
 }
 
+// Launch of one layer's attention: queries per workgroup (kFewQueries:
+// k_attn_few), keys per split (a multiple of 64) and splits.
+struct AttnPlan {
+  int qpw, n_qgroups, ks, nsplit;
+};
+
+inline AttnPlan plan_attention(bool bf16, int kmax, int nseg, const int* seg_end, const int* seg_rows, int max_seg_rows,
+                               int n_kv, int G, int hd, size_t part_entries) {
+  AttnPlan p{};
+  const int qmax = G * max_seg_rows;
+  if (bf16 && qmax <= kFewQueries) {
+    p.qpw = kFewQueries;
+    p.ks = plan_attn_few_split(kmax, nseg, seg_end, n_kv, 8 * hd, qmax, part_entries);  // K and V, hi and lo planes
+  } else {
+    p.qpw = plan_attn_queries(bf16, qmax);
+    p.ks = plan_attn_split(kmax, nseg, seg_end, seg_rows, n_kv, G, qmax, part_entries, p.qpw);
+  }
+  p.n_qgroups = (qmax + p.qpw - 1) / p.qpw;
+  p.nsplit = (kmax + p.ks - 1) / p.ks;
+  return p;
+}
+
 // Launch shape of a matmul on the wide kernel (k_wide.h): 256 or 128 output
 // rows x mt token tiles per workgroup, n_tg token groups, gk k-groups.
 struct WidePlan {
@@ -155,6 +183,10 @@ struct WidePlan {
 };
 
 constexpr int kWideMinRows = 33;  // fewer rows: the few-row kernel
+
+// The 512-row kernel (bf16): 512 output rows x 128 tokens per workgroup, batches of 4 k-steps.
+constexpr int kTiledRows = 512, kTiledTokens = 128;
+inline bool tiled_runs(int M, int N, int K) { return M > kSplitRows && N % kTiledRows == 0 && K / 32 % 4 == 0; }
 
 // Estimated time (us) of one matmul whose workgroups own `rows` output rows x
 // mt token tiles, `step` us per k-step.  Three limits overlap, combined as a
@@ -210,12 +242,14 @@ inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, 
   // the 512-row kernel where it fills its rounds: 1 - 4% under two rounds of
   // 256 rows (8B gate/up at 1024 tokens 359 against 366 us, 70B at 2047 2555
   // against 2660)
-  if (p.use && N % 512 == 0 && ksteps % 4 == 0 && plan_matmul_us(1.07, 512, 8, M, N, K, 1, 0) < best) p.use = false;
+  if (p.use && tiled_runs(M, N, K) && plan_matmul_us(1.07, kTiledRows, kTiledTokens / 16, M, N, K, 1, 0) < best)
+    p.use = false;
   return p;
 }
 
-// Launch shape of one matmul: row tiles per workgroup (nt), token tiles
-// (mtt), token groups and k-groups.  Aims for >= 384 workgroups (1.5 per CU)
+// Launch shape of one matmul that plan_wide leaves: row tiles per workgroup
+// (nt), token tiles (mtt; both only of the few-row kernel), token groups and
+// k-groups.  Aims for >= 384 workgroups (1.5 per CU)
 // with as many rows per workgroup as possible, since every workgroup reads
 // its k-range of all operand tiles; K is split across workgroups only for
 // residual-stream outputs of few-row passes (the next RMSNorm adds the
@@ -223,10 +257,10 @@ inline WidePlan plan_wide(int M, int N, int K, bool allow_split, int part_rows, 
 struct GemmPlan {
   bool tiled;  // 512-row kernel (launch_gemm_tiled)
   int nt, mtt, n_tg, gk;
-  int nw;      // waves per workgroup of the 512-row kernel
 };
 
-// The matmuls plan_wide leaves: up to 32 rows, fp32, and the large ones of the
+// The matmuls plan_wide leaves: up to 32 rows, fp32, widths that 128 does not
+// divide (a vocabulary of any multiple of 16), and the large ones of the
 // 512-row kernel.
 // part_rows: capacity of the partial buffer in rows (gk * M must fit);
 // bf16: the element type (k-steps of 32, else 16); swiglu: gate/up tile pairs.
@@ -235,7 +269,11 @@ inline GemmPlan plan_matmul(bool bf16, bool swiglu, int M, int N, int K, bool al
   const int ksteps = K / (bf16 ? 32 : 16);
   GemmPlan p{};
   p.gk = 1;
-  if (bf16 && M > kSplitRows && N % 512 == 0 && ksteps % 4 == 0) return GemmPlan{true, 4, 8, (M + 127) / 128, 1, 8};
+  if (bf16 && tiled_runs(M, N, K)) {
+    p.tiled = true;
+    p.n_tg = (M + kTiledTokens - 1) / kTiledTokens;
+    return p;
+  }
   p.mtt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
   p.n_tg = (M + 16 * p.mtt - 1) / (16 * p.mtt);
   const int nt_min = swiglu ? 2 : 1;
@@ -281,4 +319,27 @@ inline GemmPlan plan_matmul(bool bf16, bool swiglu, int M, int N, int K, bool al
   while (p.nt > nt_min && (N % (16 * p.nt) || (long long)(N / (16 * p.nt)) * p.n_tg < kTarget)) p.nt /= 2;
   while (N % (16 * p.nt)) p.nt /= 2;
   return p;
+}
+
+// Launch shape of a matmul: the wide kernel's, else plan_matmul's.
+struct MatPlan {
+  WidePlan wide;
+  GemmPlan gemm;
+  int gk() const { return wide.use ? wide.gk : gemm.gk; }
+};
+
+inline MatPlan plan_mat(bool bf16, bool swiglu, int M, int N, int K, bool allow_split, int part_rows,
+                        double split_us = 0) {
+  MatPlan p{};
+  if (bf16) p.wide = plan_wide(M, N, K, allow_split, part_rows, split_us);
+  if (!p.wide.use) p.gemm = plan_matmul(bf16, swiglu, M, N, K, allow_split, part_rows);
+  return p;
+}
+
+constexpr double kQkvSplitUs = 4.0;  // a split QKV projection's finish kernel, beside its traffic
+
+// The QKV projection: split in k-groups, or whole where that costs no more.
+inline MatPlan plan_qkv(bool bf16, int M, int N, int K, int part_rows) {
+  const MatPlan p = plan_mat(bf16, false, M, N, K, true, part_rows, kQkvSplitUs);
+  return p.gk() > 1 ? p : plan_mat(bf16, false, M, N, K, false, part_rows);
 }

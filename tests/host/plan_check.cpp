@@ -2,7 +2,8 @@
 // the benchmark workloads and at edge cases: every prefill chunk stays inside
 // the workspace and segment arrays and covers each sequence's positions once,
 // every attention launch's key split fits the partial buffer and the grid
-// limits, and every matmul launch shape is one the launchers instantiate.
+// limits, and every matmul launch shape is one the launchers instantiate.  The
+// plans are those of plan_attention, plan_mat and plan_qkv, which the passes use.
 // Built with the address and undefined-behaviour sanitizers by
 // tests/test_host_checks.py; exits non-zero on the first violation.
 #include <cstdio>
@@ -14,6 +15,7 @@
 namespace {
 
 int failures = 0;
+long long n_wide = 0, n_tiled = 0, n_few = 0;  // matmul plans by kernel
 
 #define CHECK(cond, ...)                          \
   do {                                            \
@@ -28,7 +30,8 @@ int failures = 0;
 
 struct Shape {
   const char* name;
-  int n_heads, n_kv;
+  int n_heads, n_kv, hd;
+  bool bf16;
 };
 
 // One attention launch over segments (seg_end, seg_rows): the split, the
@@ -37,17 +40,20 @@ void check_attention(const Shape& sh, int kmax, int nseg, const int* seg_end, co
                      size_t part_entries, const char* what) {
   const int G = sh.n_heads / sh.n_kv;
   const int qmax = G * max_seg_rows;
-  const int qpw = plan_attn_queries(true, qmax);
-  CHECK(qpw == 128 || qpw == 192, "%s %s: %d queries per workgroup", sh.name, what, qpw);
-  const int ks = plan_attn_split(kmax, nseg, seg_end, seg_rows, sh.n_kv, G, qmax, part_entries, qpw);
-  CHECK(ks > 0 && ks % 64 == 0, "%s %s: no key split for kmax %d", sh.name, what, kmax);
-  const long long nsplit = (kmax + ks - 1) / ks;
-  CHECK(nsplit <= kMaxKeySplits, "%s %s: %lld splits", sh.name, what, nsplit);
+  const AttnPlan p = plan_attention(sh.bf16, kmax, nseg, seg_end, seg_rows, max_seg_rows, sh.n_kv, G, sh.hd, part_entries);
+  CHECK(p.qpw == 128 || (sh.bf16 && (p.qpw == 192 || (p.qpw == 16 && qmax <= 16))), "%s %s: %d queries per workgroup",
+        sh.name, what, p.qpw);
+  CHECK((long long)p.n_qgroups * p.qpw >= qmax && (long long)(p.n_qgroups - 1) * p.qpw < qmax, "%s %s: query groups",
+        sh.name, what);
+  CHECK(p.ks > 0 && p.ks % 64 == 0, "%s %s: no key split for kmax %d", sh.name, what, kmax);
+  const long long nsplit = p.nsplit;
+  CHECK(nsplit == (kmax + p.ks - 1) / p.ks && nsplit <= kMaxKeySplits, "%s %s: %lld splits", sh.name, what, nsplit);
   // one split writes the output and no partials
   CHECK(nsplit == 1 || (size_t)nsplit * nseg * sh.n_kv * qmax <= part_entries, "%s %s: partial entries", sh.name, what);
   const long long units = nsplit * nseg * sh.n_kv;
-  const long long grid = (units + 7) / 8 * 8 * ((qmax + qpw - 1) / qpw);
+  const long long grid = (units + 7) / 8 * 8 * p.n_qgroups;
   CHECK(grid > 0 && grid < (1LL << 31), "%s %s: attention grid %lld", sh.name, what, grid);
+  CHECK(sh.bf16 || p.n_qgroups < 65536, "%s %s: fp32 attention grid", sh.name, what);
   CHECK((long long)(qmax + 3) / 4 < (1LL << 31) && (long long)nseg * sh.n_kv < 65536, "%s %s: combine grid", sh.name,
         what);
   for (int s = 0; s < nseg; ++s) CHECK(seg_end[s] <= kmax, "%s %s: segment %d ends past kmax", sh.name, what, s);
@@ -109,22 +115,31 @@ void check_verify(const Shape& sh, const std::vector<int>& L, int S, int max_blo
 // One matmul launch as planned: the shape must be one the launchers
 // instantiate, divide N into whole row groups and K into whole k-step
 // batches, fit the partial buffer and the grid limit.
-void check_matmul(const char* what, bool bf16, bool swiglu, bool allow_split, int M, int N, int K, int part_rows) {
-  const GemmPlan p = plan_matmul(bf16, swiglu, M, N, K, allow_split, part_rows);
+void check_launch(const char* what, bool bf16, bool swiglu, bool allow_split, int M, int N, int K, int part_rows,
+                  const MatPlan& mp) {
   const int ksteps = K / (bf16 ? 32 : 16);
-  CHECK(p.gk >= 1 && (p.gk == 1 || allow_split), "%s M=%d: k-groups %d", what, M, p.gk);
-  CHECK(p.gk == 1 || (long long)p.gk * M <= part_rows, "%s M=%d: %d k-groups x %d rows past %d", what, M, p.gk, M,
-        part_rows);
-  if (p.tiled) {
-    const bool known = (p.nw == 8 && (p.nt == 4 || p.nt == 2) && (p.mtt == 8 || p.mtt == 4)) ||
-                       (p.nw == 8 && p.nt == 2 && p.mtt == 6) || (p.nw == 12 && p.nt == 2 && p.mtt == 4);
-    CHECK(bf16 && known, "%s M=%d: no many-token kernel (%d waves, %d x %d)", what, M, p.nw, p.nt, p.mtt);
-    CHECK(N % (16 * p.nw * p.nt) == 0, "%s M=%d: N %d not whole row groups", what, M, N);
-    CHECK(ksteps % p.gk == 0 && (ksteps / p.gk) % 4 == 0, "%s M=%d: k-steps %d / %d", what, M, ksteps, p.gk);
-    CHECK(p.n_tg * p.mtt * 16 >= M, "%s M=%d: token groups", what, M);
-    const long long rk = (long long)(N / (16 * p.nw * p.nt)) * p.gk;
-    CHECK((rk + 7) / 8 * 8 * p.n_tg < (1LL << 31), "%s M=%d: grid", what, M);
+  const int gk = mp.gk();
+  CHECK(gk >= 1 && (gk == 1 || allow_split), "%s M=%d: k-groups %d", what, M, gk);
+  CHECK(gk == 1 || (long long)gk * M <= part_rows, "%s M=%d: %d k-groups x %d rows past %d", what, M, gk, M, part_rows);
+  const GemmPlan& p = mp.gemm;
+  if (mp.wide.use) {
+    ++n_wide;
+    const WidePlan& w = mp.wide;
+    const int rows = w.rows256 ? 256 : 128;
+    CHECK(bf16 && M >= kWideMinRows && w.mt >= 2 && w.mt <= 9, "%s M=%d: no wide kernel of %d token tiles", what, M, w.mt);
+    CHECK(N % rows == 0 && ksteps % (2 * gk) == 0, "%s M=%d: N %d, %d k-steps, %d k-groups", what, M, N, ksteps, gk);
+    CHECK(gk <= 8, "%s M=%d: %d k-groups past what the consumers add", what, M, gk);
+    CHECK((long long)w.n_tg * w.mt * 16 >= M && (long long)(N / rows) * gk * w.n_tg < (1LL << 30), "%s M=%d: token groups",
+          what, M);
+  } else if (p.tiled) {
+    ++n_tiled;
+    CHECK(bf16 && M >= kWideMinRows && p.gk == 1, "%s M=%d: no 512-row kernel (%d k-groups)", what, M, p.gk);
+    CHECK(N % 512 == 0 && ksteps % 4 == 0, "%s M=%d: N %d, %d k-steps", what, M, N, ksteps);
+    CHECK((long long)p.n_tg * 128 >= M && (long long)(N / 512) * p.n_tg < (1LL << 30), "%s M=%d: token groups", what, M);
   } else {
+    // 33 bf16 rows and more come here only where no wide shape divides the matrix
+    CHECK(!bf16 || M < kWideMinRows || N % 128, "%s M=%d: N %d left to the few-row kernel", what, M, N);
+    ++n_few;
     const bool nt_ok = p.nt == 1 || p.nt == 2 || p.nt == 4 || p.nt == 8 || ((p.nt == 3 || p.nt == 6) && p.gk > 1);
     CHECK(nt_ok && (!swiglu || (p.nt % 2 == 0)), "%s M=%d: %d row tiles", what, M, p.nt);
     CHECK((p.mtt == 1 || p.mtt == 2 || (p.mtt == 4 && p.nt <= 4)), "%s M=%d: %d token tiles with %d row tiles", what,
@@ -136,36 +151,40 @@ void check_matmul(const char* what, bool bf16, bool swiglu, bool allow_split, in
   }
 }
 
+void check_matmul(const char* what, bool bf16, bool swiglu, bool allow_split, int M, int N, int K, int part_rows) {
+  check_launch(what, bf16, swiglu, allow_split, M, N, K, part_rows,
+               plan_mat(bf16, swiglu, M, N, K, allow_split, part_rows));
+}
+
 // Every matmul of a pass over M rows (the verify block or a prefill chunk),
 // and the LM head over n_out rows.
 void check_matmuls(const char* name, bool bf16, int d, int hq, int hkv, int hd, int F, int V, int M, int n_out,
                    int part_rows) {
   const int n0 = failures;
   const int nqkv = (hq + 2 * hkv) * hd;
-  const GemmPlan q = plan_matmul(bf16, false, M, nqkv, d, true, part_rows);
-  check_matmul("qkv", bf16, false, q.gk > 1, M, nqkv, d, part_rows);
+  check_launch("qkv", bf16, false, true, M, nqkv, d, part_rows, plan_qkv(bf16, M, nqkv, d, part_rows));
   check_matmul("o", bf16, false, true, M, d, hq * hd, part_rows);
   check_matmul("gate/up", bf16, true, false, M, 2 * F, d, part_rows);
   check_matmul("down", bf16, false, true, M, d, F, part_rows);
   check_matmul("down (last, unsplit)", bf16, false, false, M, d, F, part_rows);
   if (n_out > 0) check_matmul("lm head", bf16, false, false, n_out, V, d, part_rows);
-  if (failures == n0) std::printf("%s matmuls M=%d: ok\n", name, M);
+  if (failures == n0 && M % 100 == 0) std::printf("%s matmuls M=%d: ok\n", name, M);
 }
 
-// The matmuls of a model's verify passes and prefill chunks at several row
-// counts (full and ragged chunks, the verify block of each batch).
-void check_model_matmuls(const char* name, bool bf16, int d, int hq, int hkv, int hd, int F, int V,
-                         std::vector<int> verify_rows, int batch, int max_block) {
-  const int part_rows = std::max(kMaxSplitK * kSplitRows, kMaxSplitTiled * plan_round_up(batch * max_block, 64));
-  for (int M : verify_rows) check_matmuls(name, bf16, d, hq, hkv, hd, F, V, M, 2 * 6 * batch, part_rows);
-  for (int M : {kPrefillRows, 2047, 1023, 129, 65, 64, 33, 17, 16, 1})
-    check_matmuls(name, bf16, d, hq, hkv, hd, F, V, M, 0, part_rows);
+// The matmuls of a model's verify passes and prefill chunks at every row
+// count up to the workspace's (LM-head rows as many, up to 1024).
+void check_model_matmuls(const char* name, bool bf16, int d, int hq, int hkv, int hd, int F, int V, int batch,
+                         int max_block) {
+  const int part_rows = cache_part_rows(batch, max_block), cap = cache_rows_cap(batch, max_block);
+  for (int M = 1; M <= cap; M += M < 700 || M >= cap - 2 ? 1 : std::min(13, cap - 2 - M))
+    check_matmuls(name, bf16, d, hq, hkv, hd, F, V, M, M <= 1024 ? M : 0, part_rows);
 }
 
 }  // namespace
 
 int main() {
-  const Shape s8{"8b", 32, 8}, s14{"14b", 40, 8}, s70{"70b", 64, 8}, tiny{"tiny", 4, 4};
+  const Shape s8{"8b", 32, 8, 128, true}, s14{"14b", 40, 8, 128, true}, s70{"70b", 64, 8, 128, true};
+  const Shape s1{"1b", 32, 8, 64, true}, tiny{"tiny", 4, 4, 64, false};
   // the benchmark workloads (prefix lengths as drawn: the ragged batch
   // spans 512..4096)
   check_prefill(tiny, {128}, 64, 160);
@@ -190,6 +209,15 @@ int main() {
   check_verify(s8, std::vector<int>(256, 300), 8, 8);
   check_prefill(s70, {2, 8192, 1, 4097}, 128, 8400);
   check_verify(s70, {2, 8192, 1, 4097}, 128, 128);
+  // decode steps (few queries per kv head): one row per sequence, and two
+  for (int S = 1; S <= 5; ++S) {
+    check_verify(s1, {1024}, S, 64);
+    check_verify(s1, {300, 1900, 64, 63, 65, 1, 777}, S, 64);
+    check_verify(s1, std::vector<int>(16, 1100), S, 8);
+    check_verify(s8, std::vector<int>(256, 4000), S, 8);
+    check_verify(s70, {30000}, S, 64);
+    check_verify(tiny, std::vector<int>(256, 100), S, 8);
+  }
   // one long prefix among short ones: the partials are indexed by (segment,
   // query of the longest segment), more than the rows the buffer is sized for
   std::vector<int> skewed(16, 30);
@@ -205,14 +233,22 @@ int main() {
   skewed.assign(100, 9);
   skewed[0] = 9000;
   check_prefill(s14, skewed, 64, 9100);
-  // matmul launch shapes: the benchmark models at their verify blocks
-  // (8B batch 1 and 16, 14B batch 4, 70B batch 8) and prefill chunks, and
-  // the tiny parity shapes
-  check_model_matmuls("8b", true, 4096, 32, 8, 128, 14336, 128256, {31, 496, 8 * 256}, 256, 64);
-  check_model_matmuls("14b", true, 5120, 40, 8, 128, 13824, 152064, {172}, 4, 64);
-  check_model_matmuls("70b", true, 8192, 64, 8, 128, 28672, 128256, {248, 360}, 8, 64);
-  check_model_matmuls("tiny-f32", false, 256, 4, 4, 64, 1024, 4096, {21, 84}, 4, 64);
-  check_model_matmuls("tiny-gqa-bf16", true, 256, 8, 2, 32, 768, 4096, {21, 84, 130}, 8, 64);
+  // matmul launch shapes: the benchmark models and the tiny parity shapes, and
+  // widths that the wide kernel's row groups divide partly or not at all
+  check_model_matmuls("8b", true, 4096, 32, 8, 128, 14336, 128256, 256, 64);
+  check_model_matmuls("8b", true, 4096, 32, 8, 128, 14336, 128256, 1, 64);
+  check_model_matmuls("14b", true, 5120, 40, 8, 128, 13824, 152064, 4, 64);
+  check_model_matmuls("70b", true, 8192, 64, 8, 128, 28672, 128256, 8, 64);
+  check_model_matmuls("1b", true, 2048, 32, 8, 64, 8192, 128256, 16, 8);
+  check_model_matmuls("tiny-f32", false, 256, 4, 4, 64, 1024, 4096, 4, 64);
+  check_model_matmuls("tiny-gqa-bf16", true, 256, 8, 2, 32, 768, 4096, 8, 64);
+  check_model_matmuls("d384", true, 384, 12, 12, 32, 640, 1536, 16, 72);
+  check_model_matmuls("d1280-v4112", true, 1280, 10, 1, 128, 1408, 4112, 16, 72);
+  check_model_matmuls("one-kv-head-of-32", true, 128, 4, 1, 32, 128, 16, 4, 64);
+  if (n_wide < 1000 || n_tiled < 100 || n_few < 100) {
+    std::fprintf(stderr, "plans by kernel: %lld wide, %lld 512-row, %lld few-row\n", n_wide, n_tiled, n_few);
+    ++failures;
+  }
   if (failures) {
     std::fprintf(stderr, "%d failure(s)\n", failures);
     return 1;
