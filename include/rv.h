@@ -344,6 +344,15 @@ enum { RV_MAT_QKV = 0, RV_MAT_O = 1, RV_MAT_GATEUP = 2, RV_MAT_DOWN = 3, RV_MAT_
  * untouched.  Synchronous. */
 rv_status rv_debug_time_matrix(rv_cache* c, int32_t matrix, int32_t M, int32_t reps, void* stream, float* avg_ms);
 
+/* From now on runs every matmul of 33 rows and more of this bf16 cache's calls
+ * in one launch shape instead of the planner's choice, so that each shape can
+ * be checked at small sizes: rows 128 or 256 with 2 - 9 token tiles of 16
+ * tokens and 1 - 8 k-groups (matmuls whose consumer adds no partials stay
+ * whole), or rows 512 with 8 token tiles and 1 k-group; rows = 0 returns to the
+ * planner.  A call with a matmul that the shape does not divide, or whose
+ * partials do not fit their buffer, fails with RV_E_HIP at that matmul. */
+rv_status rv_debug_force_matmul(rv_cache* c, int32_t rows, int32_t token_tiles, int32_t k_groups);
+
 /* Y[M][N] = X[M][K] . W^T with the production matrix kernel, for one stored
  * matrix (layer is ignored for RV_MAT_LM_HEAD).  Columns of Y are in logical
  * order: QKV = [q rows; k rows; v rows], GATEUP = [gate rows; up rows].

@@ -45,6 +45,7 @@ EXPORTED = [
     "rv_verify_ragged", "rv_commit_tokens", "rv_fuse_accept_noalloc",
     "rv_debug_fuse_accept", "rv_debug_output", "rv_debug_export_kv", "rv_debug_export_ids", "rv_debug_weight_bits",
     "rv_debug_linear", "rv_debug_workspace", "rv_debug_profile", "rv_debug_profile_read", "rv_debug_time_matrix",
+    "rv_debug_force_matmul",
 ]
 
 
@@ -96,6 +97,7 @@ _sig = {
     "rv_debug_workspace": ([_vp, _i32, _i32, _vp, _sz, _vp], ctypes.c_int),
     "rv_debug_profile": ([_vp, _i32], ctypes.c_int),
     "rv_debug_time_matrix": ([_vp, _i32, _i32, _i32, _vp, ctypes.POINTER(ctypes.c_float)], ctypes.c_int),
+    "rv_debug_force_matmul": ([_vp, _i32, _i32, _i32], ctypes.c_int),
     "rv_debug_profile_read": ([_vp, _i32, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(_i32)], ctypes.c_int),
 }
 for _name, (_args, _res) in _sig.items():
@@ -279,6 +281,10 @@ def rv_debug_workspace(cache: int, which: int, rows: int, dst, stream=None) -> N
 
 def rv_debug_profile(cache: int, enable: bool) -> None:
     _check(_lib.rv_debug_profile(cache, 1 if enable else 0))
+
+
+def rv_debug_force_matmul(cache: int, rows: int, token_tiles: int = 0, k_groups: int = 0) -> None:
+    _check(_lib.rv_debug_force_matmul(cache, rows, token_tiles, k_groups))
 
 
 def rv_debug_profile_read(cache: int, kclass: int):

@@ -110,6 +110,7 @@ struct rv_cache {
   uint8_t last_kb[RV_MAX_BATCH];    // its per-sequence draft counts
   int* argmax;
   int last_k = -1;
+  int force_rows = 0, force_mt = 0, force_gk = 0;  // rv_debug_force_matmul
   // event profiler
   bool prof = false;
   std::vector<hipEvent_t> prof_ev;   // pairs: start, stop
@@ -290,8 +291,25 @@ struct Prof {
   }
 };
 
+// The shape rv_debug_force_matmul asks for (the launchers refuse one that does
+// not divide the matrix; 0 k-groups: one they refuse, as the partials do not fit).
+MatPlan plan_forced(const rv_cache* c, int M, bool allow_split) {
+  MatPlan p{};
+  int gk = allow_split ? c->force_gk : 1;
+  if (gk > 1 && gk * M > c->gpart_rows) gk = 0;
+  if (c->force_rows == kTiledRows) {
+    p.gemm.tiled = true;
+    p.gemm.n_tg = (M + kTiledTokens - 1) / kTiledTokens;
+    p.gemm.gk = gk;
+  } else {
+    p.wide = WidePlan{true, c->force_rows == 256, c->force_mt, (M + 16 * c->force_mt - 1) / (16 * c->force_mt), gk};
+  }
+  return p;
+}
+
 // Launch shape of one matmul of this model.
 MatPlan plan_for(const rv_cache* c, int epi, int M, int N, int K, bool allow_split) {
+  if (c->force_rows && M >= kWideMinRows) return plan_forced(c, M, allow_split);
   return plan_mat(c->m->cfg.dtype == RV_BF16, epi == EPI_SWIGLU, M, N, K, allow_split, c->gpart_rows);
 }
 
@@ -345,7 +363,8 @@ rv_status run_layers(rv_cache* c, int M, int nseg, int max_seg_rows, int kmax, c
 
   // the same launch shapes in every layer
   const int qd = mc.n_heads * hd;
-  const MatPlan p_qkv = plan_qkv(dt == RV_BF16, M, m->qkv.N, d, c->gpart_rows);
+  const MatPlan p_qkv = c->force_rows && M >= kWideMinRows ? plan_forced(c, M, true)
+                                                           : plan_qkv(dt == RV_BF16, M, m->qkv.N, d, c->gpart_rows);
   const MatPlan p_o = plan_for(c, EPI_RESID, M, d, qd, true);
   const MatPlan p_gateup = plan_for(c, EPI_SWIGLU, M, m->gateup.N, d, false);
   const MatPlan p_down = plan_for(c, EPI_RESID, M, d, mc.ffn_dim, true);
@@ -1162,6 +1181,18 @@ rv_status rv_debug_time_matrix(rv_cache* c, int32_t matrix, int32_t M, int32_t r
   (void)hipEventDestroy(e1);
   *avg_ms = ms / reps;
   c->last_k = -1;  // workspace outputs no longer describe the last verify
+  return RV_OK;
+}
+
+rv_status rv_debug_force_matmul(rv_cache* c, int32_t rows, int32_t token_tiles, int32_t k_groups) {
+  if (!c) return rv_fail(RV_E_ARG, "cache must not be NULL");
+  const bool wide = (rows == 128 || rows == 256) && token_tiles >= 2 && token_tiles <= 9 && k_groups >= 1 && k_groups <= 8;
+  const bool tiled = rows == kTiledRows && token_tiles == kTiledTokens / 16 && k_groups == 1;
+  if (rows != 0 && !wide && !tiled) return rv_fail(RV_E_ARG, "no matrix kernel of %d rows x %d token tiles", rows, token_tiles);
+  if (rows != 0 && c->m->cfg.dtype != RV_BF16) return rv_fail(RV_E_ARG, "launch shapes are forced for bf16 models only");
+  c->force_rows = rows;
+  c->force_mt = token_tiles;
+  c->force_gk = k_groups;
   return RV_OK;
 }
 
