@@ -312,8 +312,9 @@ __global__ __launch_bounds__(NW * 64) void k_attn_bf16(AttnArgs a, int n_qg) {
 // loads, for launches that fill the 256 CUs, so that the stream does not push
 // other data out of L2 (1B pass, 32 x 1000 keys: 488 -> 468 us; 16 x 300 - 1900:
 // 1194 -> 1175); with fewer workgroups each CU's own rate counts, which they
-// lower (8B, 1 x 1024 keys: 7.6 -> 8.9 us per launch; 70B, 4 x 3000: 21 -> 28).  Passes before and after this kernel: 1B 32 x 1000
-// keys (4 layers) 579 -> 468 us, 16 x 300 - 1900 (16 layers) 1241 -> 1175.
+// lower (8B, 1 x 1024 keys: 7.6 -> 8.9 us per launch; 70B, 4 x 3000: 21 -> 28).
+// Passes before and after this kernel: 1B 32 x 1000 keys (4 layers) 579 -> 468
+// us, 16 x 300 - 1900 (16 layers) 1241 -> 1175.
 template <int HD, bool STREAM>
 __global__ __launch_bounds__(512) void k_attn_few(AttnArgs a) {
   constexpr int KT = HD == 128 ? 32 : 64;  // keys per tile: 128 registers of operands

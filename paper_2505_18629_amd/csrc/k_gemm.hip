@@ -1,6 +1,7 @@
 // Weight-streaming matrix kernel: Y[t][p] = sum_k X[t][k] W[p][k] for the
 // few-token activations of a verify block (M = batch * block rows): bf16 up to
-// 32 rows, fp32 with any number of them (more token groups); and the 512-row
+// 32 rows; with any number of them (more token groups) fp32, and bf16 widths that
+// 128 does not divide (a vocabulary of any multiple of 16); and the 512-row
 // kernel for hundreds of bf16 rows.
 //
 // Layout and schedule
@@ -147,8 +148,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_gemm(GemmArgs a) {
 // spills).  Workgroups that share rows (the token groups of a row group) have
 // consecutive items on one XCD, so the weights come from HBM about once.
 // Every load index is clamped, so the pipeline has no branches; rows past M
-// are computed and not stored.  Bound by MFMA power: 1.24 - 1.31 PFLOP/s of
-// hi/lo products at 496 - 2047 tokens, where a large library bf16 product of
+// are computed and not stored.  Bound by MFMA power: 1.26 - 1.51 PFLOP/s of
+// hi/lo products at 496 - 2047 tokens (8B gate/up 180, 346 and 696 us at 496, 1024
+// and 2047; 70B 701, 1389 and 2540), where a large library bf16 product of
 // random data reaches 1.25 - 1.48 on this part.
 template <int EPI>
 __global__ __launch_bounds__(512) void k_gemm_tiled(GemmArgs a, int items) {

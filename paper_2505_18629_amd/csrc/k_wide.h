@@ -1,7 +1,8 @@
 // Matrix kernel for 33 rows and more (bf16): Y[t][p] = sum_k X[t][k] W[p][k].
 //
-// A workgroup owns RW x NT row tiles x MT token tiles (all the tokens, where
-// they fit nine tiles) of one k-group.  Its waves have two roles:
+// A workgroup owns RW x NT row tiles x MT token tiles of one k-group: all the
+// tokens, or one of several groups of them, as plan_wide estimates cheaper.  Its
+// waves have two roles:
 //  - RW x KW consumer waves: wave (rw, kw) multiplies NT row tiles by the MT
 //    token tiles at the k-steps kw, kw + KW, ...; its weights go straight from
 //    global memory to a register ring DEPTH k-steps deep.

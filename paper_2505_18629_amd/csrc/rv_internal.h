@@ -35,7 +35,7 @@ struct GemmArgs {
   const void* X2;     //   bf16 lo plane; token tiles up to the launch's token groups are read
   int M, N, K;
   int n_tg;           // token groups of MTT*16 tokens
-  int gk;             // k-groups; (K/KT) % (4*gk) == 0
+  int gk;             // k-groups; K/KT a multiple of 4*gk (few-row kernel), 2*gk (wide), 4 (512-row, gk 1)
   float* Y;           // STORE / RESID / STORE_LOGICAL output, leading dim ldy
   int ldy;
   float* P;           // PARTIAL output [gk][M][ldy]

@@ -88,18 +88,21 @@ inline bool plan_split_fits(int ns, int groups, int qmax, size_t part_entries) {
   return ns == 1 || (ns <= kMaxKeySplits && (size_t)ns * groups * qmax <= part_entries);
 }
 
-// Key split of one attention launch (a multiple of 64 keys).  Minimises the estimated time: rounds of 256 workgroups (one per CU)
-// x (64-key tiles per workgroup + a per-workgroup overhead of about two
-// tiles; 70B batch 8 with 8K keys: 4 splits, 768 workgroups, 348 us when this was
-// chosen, 393 with 3 splits and 576) x 2.9 us per tile, counting the workgroups that have keys (segment s
+// Key split of one attention launch (a multiple of 64 keys).  Minimises the
+// estimated time: rounds of 256 workgroups (one per CU) x (64-key tiles per
+// workgroup + a per-workgroup overhead of about two tiles; 70B batch 8 with 8K
+// keys: 4 splits, 768 workgroups, 348 us when this was chosen, 393 with 3 splits
+// and 576) x 2.9 us per tile, counting the workgroups that have keys (segment s
 // has keys 0 .. seg_end[s]-1 and G * seg_rows[s] queries per kv head, in groups
 // of qpw), and for several splits the combine kernel (4 us, and 512 bytes per
 // partial and output row at 3.5 TB/s; one split needs none: 2048-row prefill
-// chunks otherwise split in two, 8B prefill 13.46 -> 13.94 ms).  Several splits
-// are bounded by the partial buffer (splits x segments x kv heads x qmax
-// entries) and by the combine kernel's kMaxKeySplits splits per query; one split
-// writes no partials and so always fits (a chunk of one long and many short
-// prefixes can have more entries than the buffer, which follows its rows).
+// chunks otherwise split in two, 8B prefill 13.46 -> 13.94 ms).  Tile time and
+// partial bytes are those of bf16 at head_dim 128; at 64 both are about half, so
+// there only the 4 us weigh too little.  Several splits are bounded by the
+// partial buffer (splits x segments x kv heads x qmax entries) and by the combine
+// kernel's kMaxKeySplits splits per query; one split writes no partials and so
+// always fits (a chunk of one long and many short prefixes can have more entries
+// than the buffer, which follows its rows).
 inline int plan_attn_split(int kmax, int nseg, const int* seg_end, const int* seg_rows, int n_kv, int G, int qmax,
                            size_t part_entries, int qpw = 128) {
   const int groups = nseg * n_kv;
