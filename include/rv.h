@@ -66,7 +66,9 @@ enum { RV_MAX_BATCH = 256, RV_MAX_DRAFTS = 32 };
  * rounded to bf16.
  * Requirements: d_model, ffn_dim and n_heads*head_dim multiples of 128;
  * head_dim 32, 64 or 128; n_heads % n_kv_heads == 0; vocab % 16 == 0 and
- * <= 262144. */
+ * <= 262144.  Prefill and verify also need d_model to be a multiple of 256 (of
+ * 512 above 4096) and at most 8192, the widths of the norm kernel; they return
+ * RV_E_HIP for others. */
 typedef struct {
   int32_t n_layers, d_model, n_heads, n_kv_heads, head_dim, ffn_dim, vocab;
   int32_t dtype;   /* RV_F32 or RV_BF16 */
